@@ -101,12 +101,12 @@ __device__ __forceinline__ long long cache_index(const Dev& d, int i, int j, int
     return ((long long)(k + d.g[2]) * d.py + (j + d.g[1])) * d.px + (i + d.g[0]);
 }
 
-template <int D, int KIND, bool NT, typename T>
+template <int D, int KIND, bool NT, bool PLAIN = false, typename T>
 __device__ __forceinline__ void face_store(T* qL, T* qR, double x, double y, double z, const Dev& d,
                                            T* __restrict__ F, long long NF, long long f)
 {
     T Fo[9];
-    face_flux<D, KIND>(qL, qR, x, y, z, f, d, Fo);
+    face_flux<D, KIND, PLAIN>(qL, qR, x, y, z, f, d, Fo);
     // the face records are read back by another kernel, not by this one: on
     // large grids (NT) nontemporal stores
     if constexpr (NT) {
@@ -142,8 +142,8 @@ __global__ __launch_bounds__(BLOCK) void k_flux_x(const T* __restrict__ Pc, T* _
         qL[v] = q1 + mc_hslope(q0, q1, q2);
         qR[v] = q2 - mc_hslope(q1, q2, q3);
     }
-    face_store<0, KIND, NT>(qL, qR, d.lo[0] + i * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1],
-                        d.lo[2] + (k + 0.5) * d.dx[2], d, F, d.nf[0], f);
+    face_store<0, KIND, NT, true>(qL, qR, d.lo[0] + i * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1],
+                                  d.lo[2] + (k + 0.5) * d.dx[2], d, F, d.nf[0], f);
 }
 
 // y or z faces: a thread marches along D over a segment of up to SEG faces at
@@ -632,7 +632,7 @@ __device__ __forceinline__ void tile_face(const T* sP, int dir, int base, int st
     } else {
         g = geo_at<KIND>(d, fx, fy, fz);
     }
-    face_solve<0>(qL, qR, geo_cast<T>(g), d, Fo);
+    face_solve_t<0>(qL, qR, geo_cast<T>(g), d, Fo);
 #pragma unroll
     for (int v = 0; v < 9; ++v)
         sF[vo[v] * nslot + slot] = Fo[v];
