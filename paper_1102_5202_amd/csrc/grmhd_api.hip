@@ -66,8 +66,10 @@ bool grid_ok(const grmhd_grid* g)
     return N <= (1LL << 38);
 }
 
+// Three primitive caches, which the substeps rotate through; one is enough for
+// the scratch of grmhd_rhs_noalloc on a 1D or 2D grid, which takes no steps.
 Layout make_layout(const grmhd_grid* g, size_t esize, bool adjoint = false, int ns = 3, int tape = 0,
-                   int ghost = 2, bool ct = false)
+                   int ghost = 2, bool ct = false, bool steps = true)
 {
     Layout L{};
     for (int d = 0; d < 3; ++d)
@@ -89,7 +91,7 @@ Layout make_layout(const grmhd_grid* g, size_t esize, bool adjoint = false, int 
     off = round_up(off + grmhd::CNT_BYTES, 256);
     for (int b = 0; b < 3; ++b) {
         L.off_pc[b] = off;
-        if (b == 0 || g->n[2] > 1)   // the extra caches serve the fused 3D update only
+        if (b == 0 || g->n[2] > 1 || steps)
             off = round_up(off + esize * 9 * (size_t)L.sv, 256);
     }
     L.off_us = off;                  // intermediate Runge-Kutta stage state
@@ -302,12 +304,34 @@ int prepare_t(grmhd_ctx* c)
         return GRMHD_OK;
     if (grmhd::launch_zero_counters(c->cnt, c->stream) != hipSuccess)
         return GRMHD_ERR_HIP;
-    for (int b = 0; b < 3; ++b)
-        if (c->d.act[2] || b == 0)
-            if (grmhd::launch_fill((T*)c->Pbuf[b], 9 * c->L.sv, std::nan(""), c->stream) != hipSuccess)
-                return GRMHD_ERR_HIP;
+    // the caches follow each other in the workspace, up to the stage state
+    const long long n = (long long)((c->L.off_us - c->L.off_pc[0]) / sizeof(T));
+    if (grmhd::launch_fill((T*)c->Pbuf[0], n, std::nan(""), c->stream) != hipSuccess)
+        return GRMHD_ERR_HIP;
     c->prepared = true;
     return GRMHD_OK;
+}
+
+// Whether the face fluxes are corrected from edge values before the update
+// (flux-CT with more than one active axis).
+bool edge_values(const grmhd_ctx* c)
+{
+    return c->d.ct && c->d.act[0] + c->d.act[1] + c->d.act[2] > 1;
+}
+
+// Which kernels a substep takes: in FP64 without edge values k_sweep (one
+// launch); mixed precision on 3D grids with MC and cleaning k_substep (one
+// launch); else the face kernels and the update.
+template <typename T>
+bool sweeps(const grmhd_ctx* c)
+{
+    return sizeof(T) == sizeof(double) && !edge_values(c);
+}
+
+template <typename T>
+bool fused(const grmhd_ctx* c)
+{
+    return sizeof(T) < sizeof(double) && c->d.act[2] && !c->d.ppm && !c->d.ct;
 }
 
 template <typename T>
@@ -344,7 +368,7 @@ int fluxes(grmhd_ctx* c, int b, int ndir)
         if (rc)
             return rc;
     }
-    if (c->d.ct && ndir == 3) {
+    if (edge_values(c) && ndir == 3) {
         T* F[3] = {faces<T>(c, 0), faces<T>(c, 1), faces<T>(c, 2)};
         T* W[3] = {(T*)c->W[0], (T*)c->W[1], (T*)c->W[2]};
         rc = timed(c, GRMHD_K_CT, [&] { return grmhd::launch_ct(F, W, c->d, c->stream); });
@@ -384,12 +408,27 @@ int prim_t(grmhd_ctx* c, const double* U, double* P)
     return GRMHD_OK;
 }
 
+// Right-hand side of P.  Where k_sweep serves, one launch does all of it from P
+// itself (keep: it also loads P into the context's cache); else the cache is
+// loaded and the face kernels run.
 template <typename T>
-int rhs_t(grmhd_ctx* c, const double* P, double* R)
+int rhs_t(grmhd_ctx* c, const double* P, double* R, bool keep = true)
 {
-    int rc = prepare_t<T>(c);
+    int rc = keep || !sweeps<T>(c) ? prepare_t<T>(c) : GRMHD_OK;
     if (rc)
         return rc;
+    if (sweeps<T>(c)) {
+        grmhd::SweepArgs A{};
+        A.P = P;
+        A.R = R;
+        A.Pn = keep ? cache<double>(c) : nullptr;
+        rc = timed(c, GRMHD_K_RHS, [&] { return grmhd::launch_sweep(c->kind, A, c->d, c->stream); });
+        if (rc)
+            return rc;
+        c->cache_valid = true;
+        c->ghosts_ok[0] = true;
+        return GRMHD_OK;
+    }
     rc = timed(c, GRMHD_K_CONS, [&] {
         return grmhd::launch_cons(c->kind, P, (double*)nullptr, cache<T>(c), c->d, c->stream);
     });
@@ -412,19 +451,39 @@ const double RK3B[3] = {1.0, 0.25, 2.0 / 3.0};
 const double RK2A[2] = {0.0, 0.5};
 const double RK2B[2] = {1.0, 0.5};
 
-// One substep's update launch with the stage-state types TS (read) and TO
-// (written).
+// One FP64 substep in one launch: the primitives Pc to Pn, the stage state Us
+// (null: U^n) to Uo.
+int sweep_stage(grmhd_ctx* c, const double* Pc, double* Pn, const double* Un, const double* Us, double* Uo, double dt,
+                double a, double b, unsigned char* fout)
+{
+    grmhd::SweepArgs A{};
+    A.Pc = Pc;
+    A.Pn = Pn;
+    A.Un = Un;
+    A.Us = Us;
+    A.Uo = Uo;
+    A.cnt = c->cnt;
+    A.fout = fout;
+    A.dt = dt;
+    A.a = a;
+    A.b = b;
+    return timed(c, GRMHD_K_UPDATE, [&] { return grmhd::launch_sweep(c->kind, A, c->d, c->stream); });
+}
+
+// The update launch of the other substeps, with the stage-state types TS (read)
+// and TO (written).
 template <typename T, typename TS, typename TO>
-int update_stage(grmhd_ctx* c, bool fused, int src, int dst, const double* U, const TS* Us, TO* Uout,
-                 double dt, double a, double b)
+int update_stage(grmhd_ctx* c, int src, int dst, const double* U, const TS* Us, TO* Uout, double dt, double a,
+                 double b)
 {
     return timed(c, GRMHD_K_UPDATE, [&] {
-        if (fused)
-            return grmhd::launch_substep(c->kind, (const T*)cache<T>(c, src), cache<T>(c, dst), U, Us, Uout, c->d,
-                                         dt, a, b, c->cnt, (unsigned char*)nullptr, c->stream);
+        if constexpr (sizeof(T) < sizeof(double))
+            if (fused<T>(c))
+                return grmhd::launch_substep(c->kind, (const T*)cache<T>(c, src), cache<T>(c, dst), U, Us, Uout, c->d,
+                                             dt, a, b, c->cnt, (unsigned char*)nullptr, c->stream);
         return grmhd::launch_update(c->kind, (const T*)faces<T>(c, 0), (const T*)faces<T>(c, 1),
-                                    (const T*)faces<T>(c, 2), (const T*)cache<T>(c, src), cache<T>(c, dst), U,
-                                    Us, Uout, c->d, dt, a, b, c->cnt, (unsigned char*)nullptr, c->stream);
+                                    (const T*)faces<T>(c, 2), (const T*)cache<T>(c, src), cache<T>(c, dst), U, Us,
+                                    Uout, c->d, dt, a, b, c->cnt, (unsigned char*)nullptr, c->stream);
     });
 }
 
@@ -434,27 +493,29 @@ int step_t(grmhd_ctx* c, double* U, double dt)
     const int ns = c->rk_order;
     const double* A = ns == 3 ? RK3A : RK2A;
     const double* B = ns == 3 ? RK3B : RK2B;
-    // 3D grids with MC and cleaning: one launch of the fused substep kernel
-    // (the faces of every axis, the differences, sources, RK combination and
-    // recovery), which writes the new primitives to another cache; otherwise
-    // (1D, 2D, PPM, flux-CT) the face kernels and then the update in place on
-    // the cache (for flux-CT with the face fluxes corrected in between).  The first stage
+    // The kernels of one launch a substep write the new primitives to another
+    // cache; the face kernels are followed by the update in place on the cache
+    // (for flux-CT with the face fluxes corrected in between).  The first stage
     // reads U^n as its stage state; the intermediate stage state has the cache
     // type (float in the mixed path); the last stage writes U.
-    const bool fused = c->d.act[2] && !c->d.ppm && !c->d.ct;
+    const bool rotate = sweeps<T>(c) || fused<T>(c);
     T* Us = (T*)c->Us;
     for (int s = 0; s < ns; ++s) {
-        const int src = fused ? s : 0;
-        const int dst = fused ? (s == ns - 1 ? 0 : s + 1) : 0;
-        int rc = fluxes<T>(c, src, fused ? 0 : 3);
+        const bool first = s == 0, last = s == ns - 1;
+        const int src = rotate ? s : 0;
+        const int dst = rotate && !last ? s + 1 : 0;
+        int rc = fluxes<T>(c, src, rotate ? 0 : 3);
         if (rc)
             return rc;
-        if (s == 0)
-            rc = update_stage<T>(c, fused, src, dst, U, (const double*)U, Us, dt, A[s], B[s]);
-        else if (s < ns - 1)
-            rc = update_stage<T>(c, fused, src, dst, U, (const T*)Us, Us, dt, A[s], B[s]);
+        if (sweeps<T>(c))
+            rc = sweep_stage(c, cache<double>(c, src), cache<double>(c, dst), U, first ? nullptr : (double*)Us,
+                             last ? U : (double*)Us, dt, A[s], B[s], nullptr);
+        else if (first)
+            rc = update_stage<T>(c, src, dst, U, (const double*)U, Us, dt, A[s], B[s]);
+        else if (!last)
+            rc = update_stage<T>(c, src, dst, U, (const T*)Us, Us, dt, A[s], B[s]);
         else
-            rc = update_stage<T>(c, fused, src, dst, U, (const T*)Us, U, dt, A[s], B[s]);
+            rc = update_stage<T>(c, src, dst, U, (const T*)Us, U, dt, A[s], B[s]);
         if (rc)
             return rc;
         c->ghosts_ok[dst] = true;
@@ -491,33 +552,14 @@ int adj_prepare(grmhd_ctx* c)
 int adj_recompute(grmhd_ctx* c, const double* U, double dt, const double* A, const double* B)
 {
     const int ns = c->rk_order;
-    const bool fused = c->d.act[2] && !c->d.ppm && !c->d.ct;
     int rc = timed(c, GRMHD_K_PRIM, [&] {
         return grmhd::launch_prim(c->kind, U, c->Pb, c->Ac[0], c->d, c->cnt, c->stream);
     });
     if (rc)
         return rc;
     for (int s = 0; s < ns; ++s) {
-        const double* Ps = c->Ac[s];
-        for (int dir = 0; dir < (fused ? 0 : 3); ++dir) {
-            if (!c->d.act[dir])
-                continue;
-            rc = timed(c, GRMHD_K_FLUX_X + dir, [&] {
-                return grmhd::launch_flux(c->kind, dir, Ps, (double*)c->F[dir], c->d, c->stream);
-            });
-            if (rc)
-                return rc;
-        }
-        const double* Us = s == 0 ? U : c->Aus;
-        unsigned char* fl = c->Aflags + (size_t)s * c->L.N;
-        rc = timed(c, GRMHD_K_UPDATE, [&] {
-            if (fused)
-                return grmhd::launch_substep(c->kind, Ps, c->Ac[s + 1], U, Us, c->Aus, c->d, dt, A[s], B[s], c->cnt,
-                                             fl, c->stream);
-            return grmhd::launch_update(c->kind, (const double*)c->F[0], (const double*)c->F[1],
-                                        (const double*)c->F[2], Ps, c->Ac[s + 1], U, Us, c->Aus, c->d, dt,
-                                        A[s], B[s], c->cnt, fl, c->stream);
-        });
+        rc = sweep_stage(c, c->Ac[s], c->Ac[s + 1], U, s == 0 ? nullptr : c->Aus, c->Aus, dt, A[s], B[s],
+                         c->Aflags + (size_t)s * c->L.N);
         if (rc)
             return rc;
     }
@@ -596,7 +638,6 @@ int step_record(grmhd_ctx* c, double* U, double dt, int slot)
     const int ns = c->rk_order;
     const double* A = ns == 3 ? RK3A : RK2A;
     const double* B = ns == 3 ? RK3B : RK2B;
-    const bool fused = c->d.act[2] && !c->d.ppm && !c->d.ct;
     const size_t bytes = sizeof(double) * 9 * (size_t)c->L.sv;
     int rc = GRMHD_OK;
     if (!c->ghosts_ok[0]) {
@@ -611,28 +652,8 @@ int step_record(grmhd_ctx* c, double* U, double dt, int slot)
     double* Us = (double*)c->Us;
     unsigned char* fl = tape_flags(c, slot);
     for (int s = 0; s < ns; ++s) {
-        const double* Ps = tape_cache(c, slot, s);
-        double* Pn = tape_cache(c, slot, s + 1);
-        for (int dir = 0; dir < (fused ? 0 : 3); ++dir) {
-            if (!c->d.act[dir])
-                continue;
-            rc = timed(c, GRMHD_K_FLUX_X + dir, [&] {
-                return grmhd::launch_flux(c->kind, dir, Ps, (double*)c->F[dir], c->d, c->stream);
-            });
-            if (rc)
-                return rc;
-        }
-        const double* Uin = s == 0 ? U : Us;
-        double* Uo = s == ns - 1 ? U : Us;
-        unsigned char* f = fl + (size_t)s * c->L.N;
-        rc = timed(c, GRMHD_K_UPDATE, [&] {
-            if (fused)
-                return grmhd::launch_substep(c->kind, Ps, Pn, U, Uin, Uo, c->d, dt, A[s], B[s], c->cnt, f,
-                                             c->stream);
-            return grmhd::launch_update(c->kind, (const double*)c->F[0], (const double*)c->F[1],
-                                        (const double*)c->F[2], Ps, Pn, U, Uin, Uo, c->d, dt, A[s], B[s],
-                                        c->cnt, f, c->stream);
-        });
+        rc = sweep_stage(c, tape_cache(c, slot, s), tape_cache(c, slot, s + 1), U, s == 0 ? nullptr : Us,
+                         s == ns - 1 ? U : Us, dt, A[s], B[s], fl + (size_t)s * c->L.N);
         if (rc)
             return rc;
     }
@@ -674,9 +695,9 @@ size_t grmhd_workspace_bytes(const grmhd_grid* grid, const grmhd_opts* opts)
 namespace {
 
 // Validate the arguments of grmhd_init and fill the (host-side) context c,
-// whose workspace is opts->workspace.
+// whose workspace is opts->workspace (steps: large enough to take steps).
 int init_ctx(grmhd_ctx* c, const grmhd_metric* metric, const grmhd_grid* grid, const grmhd_eos* eos,
-             const grmhd_opts* opts)
+             const grmhd_opts* opts, bool steps = true)
 {
     if (!grid_ok(grid))
         return GRMHD_ERR_ARG;
@@ -710,7 +731,7 @@ int init_ctx(grmhd_ctx* c, const grmhd_metric* metric, const grmhd_grid* grid, c
     if (!opts_fit(grid, opts))
         return GRMHD_ERR_ARG;
     Layout L = make_layout(grid, elem_size(opts), wants_adjoint(opts), opts->rk_order, tape_slots(opts),
-                           ghost_width(opts), opts->divergence == GRMHD_DIV_FLUXCT);
+                           ghost_width(opts), opts->divergence == GRMHD_DIV_FLUXCT, steps);
     if (!opts->workspace || opts->workspace_bytes < L.total)
         return GRMHD_ERR_WORKSPACE;
     if (((uintptr_t)opts->workspace) % 256 != 0)
@@ -925,9 +946,9 @@ int grmhd_rhs_noalloc(const grmhd_metric* metric, const grmhd_grid* grid, const 
     o.tape_steps = 0;
     if (!grid_ok(grid) || !opts_fit(grid, &o))
         return GRMHD_ERR_ARG;
-    const size_t need = grmhd_workspace_bytes(grid, &o);
-    if (need == 0)
-        return GRMHD_ERR_ARG;
+    const size_t need = make_layout(grid, elem_size(&o), false, o.rk_order == 2 ? 2 : 3, 0, ghost_width(&o),
+                                    o.divergence == GRMHD_DIV_FLUXCT, false)
+                            .total;
     if (need > GRMHD_NOALLOC_SCRATCH_BYTES)
         return GRMHD_ERR_WORKSPACE;
     void* base = noalloc_base();
@@ -937,11 +958,11 @@ int grmhd_rhs_noalloc(const grmhd_metric* metric, const grmhd_grid* grid, const 
     o.workspace_bytes = GRMHD_NOALLOC_SCRATCH_BYTES;
     // a context on the stack (no timing, no adjoint: nothing of it allocates)
     grmhd_ctx c;
-    int rc = init_ctx(&c, metric, grid, eos, &o);
+    int rc = init_ctx(&c, metric, grid, eos, &o, false);
     if (rc)
         return rc;
     c.stream = (hipStream_t)stream;
-    return c.mixed ? rhs_t<float>(&c, P, R) : rhs_t<double>(&c, P, R);
+    return c.mixed ? rhs_t<float>(&c, P, R, false) : rhs_t<double>(&c, P, R, false);
 }
 
 int grmhd_step(grmhd_ctx* c, double* U, double dt)

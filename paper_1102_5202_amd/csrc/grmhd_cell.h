@@ -1,0 +1,70 @@
+// grmhd_cell.h -- device functions shared by the kernels that update cells.
+#pragma once
+
+#include "grmhd_device.h"
+
+namespace grmhd {
+
+// The kernel's arguments (one struct S), loaded anew: a plane's work uses more
+// uniform values than there are scalar registers, and values kept from the
+// kernel's start would live in vector registers' lanes, one vector instruction a
+// read.
+template <class S>
+__device__ __forceinline__ S kernel_args()
+{
+    auto p = (const __attribute__((address_space(4))) S*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    S k;
+    __builtin_memcpy(&k, p, sizeof k);
+    return k;
+}
+
+__device__ __forceinline__ long long cache_index(const Dev& d, int i, int j, int k)
+{
+    return ((long long)(k + d.g[2]) * d.py + (j + d.g[1])) * d.px + (i + d.g[0]);
+}
+
+// Store the primitives of cell (i, j, k) at cache position pc, and at the
+// ghost positions whose boundary rule copies this cell, so that the cache
+// leaves the kernel with its ghost slabs filled (only the face slabs are
+// ghosts: every stencil is 1D).  Periodic: the cell is the image of ghost
+// idx + n when idx < g and of ghost idx - n when idx >= n - g.  Outflow
+// (zero gradient): the first and last cells fill both ghost layers beside
+// them.  Active axes have n >= g, so these are all the images.
+template <typename T>
+__device__ __forceinline__ void store_prim(const Dev& d, T* __restrict__ P, long long pc, int i, int j,
+                                           int k, const double* p)
+{
+#pragma unroll
+    for (int v = 0; v < 9; ++v)
+        P[v * d.sv + pc] = (T)p[v];
+    const int idx[3] = {i, j, k};
+    const long long stride[3] = {1, d.px, (long long)d.px * d.py};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        if (!d.act[a])
+            continue;
+        const int n = d.n[a], g = d.g[a];
+        const long long st = stride[a];
+        if (d.bc[a] == 0) {
+            if (idx[a] < g) {
+#pragma unroll
+                for (int v = 0; v < 9; ++v)
+                    P[v * d.sv + pc + n * st] = (T)p[v];
+            }
+            if (idx[a] >= n - g) {
+#pragma unroll
+                for (int v = 0; v < 9; ++v)
+                    P[v * d.sv + pc - n * st] = (T)p[v];
+            }
+        } else if (idx[a] == 0 || idx[a] == n - 1) {
+            const long long s1 = idx[a] == 0 ? -st : st;
+            for (int e = 1; e <= g; ++e)
+#pragma unroll
+                for (int v = 0; v < 9; ++v)
+                    P[v * d.sv + pc + e * s1] = (T)p[v];
+        }
+    }
+}
+
+}  // namespace grmhd

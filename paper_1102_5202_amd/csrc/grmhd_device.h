@@ -42,6 +42,31 @@ struct Dev {
     const double* mf[3];
 };
 
+// Square roots and the reciprocal of positive normal doubles, without the range
+// scaling of the library forms (arguments here are far from the ends of the
+// exponent range): the hardware estimate refined to within an ulp.
+__device__ __forceinline__ double fast_rsqrt(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+__device__ __forceinline__ double fast_sqrt(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x), h = 0.5 * y;
+    double g = x * y;
+    g = fma(g, fma(-h, g, 0.5), g);
+    return fma(fma(-g, g, x), h, g);
+}
+
+__device__ __forceinline__ double fast_rcp(double x)
+{
+    const double r = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, r, 1.0);
+    return fma(r, fma(e, e, e), r);
+}
+
 // Geometry at one point.
 struct Geo {
     double alpha, psi4, ipsi4, sqrtg, sqrtmg, isqrtmg;
@@ -53,10 +78,10 @@ __device__ __forceinline__ double soft_iradius(const Dev& d, double r2, bool& va
 {
     if (d.soft == 0) {
         varying = true;
-        return rsqrt(r2 + d.rmin2);
+        return fast_rsqrt(r2 + d.rmin2);
     }
     varying = r2 > d.rmin2;
-    return rsqrt(varying ? r2 : d.rmin2);
+    return fast_rsqrt(varying ? r2 : d.rmin2);
 }
 
 // The isotropic metric from h = M / (2 r_s) < 1: alpha = (1-h)/(1+h),
@@ -64,7 +89,7 @@ __device__ __forceinline__ double soft_iradius(const Dev& d, double r2, bool& va
 __device__ __forceinline__ Geo geo_from_h(double h, double& i1h)
 {
     Geo g;
-    const double q = 1.0 / ((1.0 - h) * (1.0 + h));
+    const double q = fast_rcp((1.0 - h) * (1.0 + h));
     i1h = (1.0 - h) * q;                  // 1 / (1 + h)
     const double im1h = (1.0 + h) * q;    // 1 / (1 - h)
     const double psi = 1.0 + h;
@@ -316,26 +341,6 @@ __device__ __forceinline__ bool finite(double x)
 }
 
 // ---------------------------------------------------------------------------
-// Square roots and the reciprocal of positive normal doubles, without the range
-// scaling of the library forms (arguments here are far from the ends of the
-// exponent range): the hardware estimate refined to within an ulp.
-__device__ __forceinline__ double fast_rsqrt(double x)
-{
-    const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-x * y, y, 1.0);
-    return fma(y * e, fma(e, 0.375, 0.5), y);
-}
-
-__device__ __forceinline__ double fast_sqrt(double x)
-{
-    const double y = __builtin_amdgcn_rsq(x);
-    double g = x * y, h = 0.5 * y;
-    const double r = fma(-h, g, 0.5);
-    g = fma(g, r, g);
-    h = fma(h, r, h);
-    return fma(fma(-g, g, x), h, g);
-}
-
 // The face solver regrouped for FP64 (issue-bound: about a third of a face's
 // instructions were divisions, square roots and repeated products).  Per state
 // one reciprocal square root, one reciprocal and one square root remain of two
@@ -378,7 +383,7 @@ __device__ __forceinline__ FaceState face_state(const double* q, double Bn, cons
     // the dispersion relation with the isotropic fast speed
     // c^2 = (gamma p + b^2) / wtot, scaled by wtot (W^2 (1 - c^2) + c^2)
     const double an = w - gp, cn = b2 + gp;
-    const double idn = 1.0 / (W2 * an + cn);
+    const double idn = fast_rcp(W2 * an + cn);
     const double t = uD * (an * idn);
     const double s = fast_sqrt(fmax(cn * idn * (g.ipsi4 - uD * t), 1e-290));
     k.lp = W * t + s;
@@ -418,7 +423,7 @@ __device__ __forceinline__ void face_solve64(const double* qL, const double* qR,
     // In this form equal fluxes and states return the flux itself, whatever
     // the rounding of the weights, so that matter at rest in a uniform field
     // stays exactly at rest.
-    const double cR0 = -sl / (sr - sl);
+    const double cR0 = -sl * fast_rcp(sr - sl);
     const double cR = sl == 0.0 ? 0.0 : (sr == 0.0 ? 1.0 : cR0);
     const double cU = sl == 0.0 ? 0.0 : -sr * cR;
 #pragma unroll
@@ -585,9 +590,9 @@ __device__ __forceinline__ bool c2p_newton2d(const C2P& c, double gk, double tol
     for (int it = 0; it < maxit; ++it) {
         iters = it + 1;
         double bw = c.Bc2 + Wc;
-        double iW = 1.0 / Wc;
+        double iW = fast_rcp(Wc);
         double iW2 = iW * iW;
-        double is = rsqrt(1.0 - v2);          // 1 / sqrt(1 - v^2) = W
+        double is = fast_rsqrt(1.0 - v2);     // 1 / sqrt(1 - v^2) = W
         double s = (1.0 - v2) * is;
         // residuals
         double r1 = v2 * bw * bw - c.QB2 * (c.Bc2 + 2.0 * Wc) * iW2 - c.Qt2;
@@ -598,7 +603,7 @@ __device__ __forceinline__ bool c2p_newton2d(const C2P& c, double gk, double tol
         double a12 = bw * bw;
         double a21 = -c.QB2 * iW2 * iW - 1.0 + gk * (1.0 - v2);
         double a22 = -0.5 * c.Bc2 + gk * (-Wc + 0.5 * c.D * is);
-        double idet = 1.0 / (a11 * a22 - a12 * a21);
+        double idet = fast_rcp(a11 * a22 - a12 * a21);
         double dW = (r1 * a22 - a12 * r2) * idet;
         double dv = (a11 * r2 - a21 * r1) * idet;
         double Wn = Wc - dW;
@@ -851,7 +856,7 @@ __device__ __forceinline__ int recover_cell(const Dev& d, const Geo& g, double* 
         }
     }
     if (ok) {
-        double W = rsqrt(1.0 - v2);
+        double W = fast_rsqrt(1.0 - v2);
         double s = (1.0 - v2) * W;
         p[0] = c.D * s;
         p[1] = d.gk * (Wc * (1.0 - v2) - c.D * s);

@@ -43,13 +43,29 @@ template <typename T, typename TS, typename TO>
 hipError_t launch_update(int kind, const T* Fx, const T* Fy, const T* Fz, const T* Pc, T* Pn, const double* Un,
                          const TS* Us, TO* Uout, const Dev& d, double dt, double a, double b,
                          unsigned long long* cnt, unsigned char* fout, hipStream_t s);
-// The whole substep of a 3D grid (MC, cleaning) in one launch: faces of all
-// three axes, flux differences, sources, RK combination and recovery; reads
+// The whole substep of a 3D grid (mixed precision, MC, cleaning) in one launch:
+// faces of all three axes, flux differences, sources, RK combination and recovery; reads
 // the primitives from Pc, writes the new ones (with ghost images) to Pn.
 template <typename T, typename TS, typename TO>
 hipError_t launch_substep(int kind, const T* Pc, T* Pn, const double* Un, const TS* Us, TO* Uout, const Dev& d,
                           double dt, double a, double b, unsigned long long* cnt, unsigned char* fout,
                           hipStream_t s);
+// One FP64 substep, or one right-hand side (R set), of a grid in one launch
+// (grmhd_sweep.hip).
+struct SweepArgs {
+    const double* Pc;   // substep: the primitives (ghosted cache)
+    const double* P;    // right-hand side: the caller's primitives (dense)
+    double* Pn;         // the new primitives (another cache); right-hand side: P's copy, or null
+    const double* Un;   // U^n
+    const double* Us;   // U^s, or null: the first stage's, U^n
+    double* Uo;         // U^(s+1)
+    double* R;
+    unsigned long long* cnt;
+    unsigned char* fout;   // may be null: per-cell recovery flags
+    double dt, a, b;
+    int ngrp, nseg, seg;   // set by launch_sweep
+};
+hipError_t launch_sweep(int kind, const SweepArgs& A, const Dev& d, hipStream_t s);
 template <typename T>
 hipError_t launch_rhs(int kind, const T* Fx, const T* Fy, const T* Fz, const T* Pc, double* R,
                       const Dev& d, hipStream_t s);

@@ -1,19 +1,20 @@
 // grmhd_kernels.hip -- HIP kernels of the GRMHD substep (gfx950, wave64).
 //
-// One substep (section 2.2 of the paper) on a 3D grid is one launch of
-// k_substep: per tile of z columns and plane, the primitives staged in LDS,
-// MC reconstruction of the 9 primitives, exact (normal field, Phi) cleaning
-// pair, face physics of both states and HLLE flux (section 3.2) for the x and
-// y faces from LDS and for the z faces from a register window, then per cell
-// the flux differences, metric sources (eq. 2), SSP Runge-Kutta combination,
-// Newton recovery of the primitives with the atmosphere/floor policy and the
-// status counters.  Every kernel that writes primitives also writes their
-// ghost images, so the ghost pass k_ghosts runs only for caches filled
-// otherwise.  1D and 2D grids, PPM (k_flux_ppm) and flux-CT (k_ct_edges,
-// k_ct_faces) use face kernels per active axis (k_flux_x, k_flux_march) and the
-// cell kernel k_update.  Also here: the stored metric's set-up (k_metric), the
-// single-kernel maps (k_cons, k_prim, k_rhs) and the batched 1D ensemble
-// (k_batch_*).
+// One substep (section 2.2 of the paper) takes MC or PPM reconstruction of the 9
+// primitives, the exact (normal field, Phi) cleaning pair, face physics of both
+// states and HLLE flux (section 3.2) for the faces of every active axis, then per
+// cell the flux differences, metric sources (eq. 2), SSP Runge-Kutta
+// combination, Newton recovery of the primitives with the atmosphere/floor
+// policy and the status counters.  In FP64 that is one launch of k_sweep
+// (grmhd_sweep.hip).  Here: mixed precision on 3D grids in one launch of
+// k_substep (x and y faces from planes staged in LDS, z faces from a register
+// window); mixed precision on 1D and 2D grids or with PPM, and flux-CT
+// (k_ct_edges, k_ct_faces), with face kernels per active axis (k_flux_x,
+// k_flux_march, k_flux_ppm) and the cell kernel k_update.  Every kernel that
+// writes primitives also writes their ghost images, so the ghost pass k_ghosts
+// runs only for caches filled otherwise.  Also here: the stored metric's set-up
+// (k_metric), the single-kernel maps (k_cons, k_prim, k_rhs) and the batched 1D
+// ensemble (k_batch_*).
 //
 // T is the type of the primitive caches, the face fluxes and the face physics:
 // double (FP64 path) or float (mixed precision).  The metric is always
@@ -22,6 +23,7 @@
 //
 // Threads are mapped over faces (cells), x fastest, so every load and store of
 // the structure-of-arrays buffers is coalesced.
+#include "grmhd_cell.h"
 #include "grmhd_device.h"
 #include "grmhd_internal.h"
 
@@ -94,11 +96,6 @@ __global__ __launch_bounds__(BLOCK) void k_ghosts(T* __restrict__ Pc, Dev d, lon
 #pragma unroll
     for (int v = 0; v < 9; ++v)
         Pc[v * d.sv + dst] = Pc[v * d.sv + sp];
-}
-
-__device__ __forceinline__ long long cache_index(const Dev& d, int i, int j, int k)
-{
-    return ((long long)(k + d.g[2]) * d.py + (j + d.g[1])) * d.px + (i + d.g[0]);
 }
 
 template <int D, int KIND, bool NT, bool PLAIN = false, typename T>
@@ -427,49 +424,6 @@ __device__ __forceinline__ void tally(int flags, int iters, int& nf, int& na, in
     itmax = max(itmax, iters);
 }
 
-// Store the primitives of cell (i, j, k) at cache position pc, and at the
-// ghost positions whose boundary rule copies this cell, so that the cache
-// leaves the kernel with its ghost slabs filled (only the face slabs are
-// ghosts: every stencil is 1D).  Periodic: the cell is the image of ghost
-// idx + n when idx < g and of ghost idx - n when idx >= n - g.  Outflow
-// (zero gradient): the first and last cells fill both ghost layers beside
-// them.  Active axes have n >= g, so these are all the images.
-template <typename T>
-__device__ __forceinline__ void store_prim(const Dev& d, T* __restrict__ P, long long pc, int i, int j,
-                                           int k, const double* p)
-{
-#pragma unroll
-    for (int v = 0; v < 9; ++v)
-        P[v * d.sv + pc] = (T)p[v];
-    const int idx[3] = {i, j, k};
-    const long long stride[3] = {1, d.px, (long long)d.px * d.py};
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        if (!d.act[a])
-            continue;
-        const int n = d.n[a], g = d.g[a];
-        const long long st = stride[a];
-        if (d.bc[a] == 0) {
-            if (idx[a] < g) {
-#pragma unroll
-                for (int v = 0; v < 9; ++v)
-                    P[v * d.sv + pc + n * st] = (T)p[v];
-            }
-            if (idx[a] >= n - g) {
-#pragma unroll
-                for (int v = 0; v < 9; ++v)
-                    P[v * d.sv + pc - n * st] = (T)p[v];
-            }
-        } else if (idx[a] == 0 || idx[a] == n - 1) {
-            const long long s1 = idx[a] == 0 ? -st : st;
-            for (int e = 1; e <= g; ++e)
-#pragma unroll
-                for (int v = 0; v < 9; ++v)
-                    P[v * d.sv + pc + e * s1] = (T)p[v];
-        }
-    }
-}
-
 // The stage inputs of cell c: U^n and U^s.  U^n, U^s and U^(s+1) are touched
 // once per cell and substep: on large grids (NT) nontemporal accesses keep them
 // from displacing the face records and primitives that neighbouring
@@ -534,7 +488,7 @@ __device__ __forceinline__ int stage_cell(const Dev& d, const Geo& g, const doub
     return stage_finish<NT>(d, g, R, q, un, us, Uout, c, Pout, pc, i, j, k, dt, a, b, fout, iters);
 }
 
-// 1D/2D update: flux differences, sources, RK combination and recovery of the
+// Update after the face kernels: flux differences, sources, RK combination and recovery of the
 // primitives for every cell.  The cell's primitives are read from Pc and the
 // new ones written to Pn (which may be Pc: each thread reads only its own cell).
 template <int KIND, bool NT, typename T, typename TS, typename TO>
@@ -568,7 +522,8 @@ __global__ __launch_bounds__(BLOCK) void k_update(const T* __restrict__ Fx, cons
 }
 
 // ---------------------------------------------------------------------------
-// The whole substep of a 3D grid in one kernel (MC reconstruction, cleaning).
+// The whole substep of a 3D grid in one kernel (mixed precision, MC
+// reconstruction, cleaning).
 // A workgroup owns a TX x TY tile of z columns and a segment of SEG planes and
 // walks the planes upwards.  For plane k it
 //   (1) stages the primitives of the tile and of a 2-cell halo in x and y (the
@@ -638,22 +593,37 @@ __device__ __forceinline__ void tile_face(const T* sP, int dir, int base, int st
         sF[vo[v] * nslot + slot] = Fo[v];
 }
 
+template <typename T, typename TS, typename TO>
+struct SubstepArgs {
+    const T* Pc;
+    T* Pn;
+    const double* Un;
+    const TS* Us;
+    TO* Uout;
+    double dt, a, b;
+    unsigned long long* cnt;
+    unsigned char* fout;
+    int ntx, ntiles;
+    Dev d;
+};
+
 template <int KIND, int TX, int TY, int SEG, bool NT, typename T, typename TS, typename TO>
 __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_substep(
-    const T* __restrict__ Pc, T* __restrict__ Pn, const double* Un, const TS* Us, TO* Uout, Dev d, double dt,
-    double a, double b, unsigned long long* __restrict__ cnt, unsigned char* __restrict__ fout, int ntx, int ntiles)
+    SubstepArgs<T, TS, TO>)
 {
     using G = Tile<TX, TY>;
-    // With a float cache the staged planes and the face fluxes are double
-    // buffered (70.8 KB of LDS, still two workgroups per CU): the faces of
-    // plane k + 1 and the update of plane k then share one barrier interval.
-    // With a double cache that would take 141.7 KB, one workgroup per CU, so
-    // each plane has its staging, faces and update between two barriers.
-    constexpr bool DB = sizeof(T) < sizeof(double);
-    constexpr int NB = DB ? 2 : 1;
-    __shared__ T sP[NB][9 * G::PLANE];
-    __shared__ T sFx[NB][9 * G::NFX];
-    __shared__ T sFy[NB][9 * G::NFY];
+    using Args = SubstepArgs<T, TS, TO>;
+    const Args K0 = kernel_args<Args>();
+    const Dev& d = K0.d;
+    const T* Pc = K0.Pc;
+    const int ntx = K0.ntx, ntiles = K0.ntiles;
+    // The staged planes and the face fluxes are double buffered (70.8 KB of
+    // LDS, two workgroups per CU): the faces of plane k + 1 and the update of
+    // plane k share one barrier interval.
+    static_assert(sizeof(T) == sizeof(float), "mixed precision");
+    __shared__ T sP[2][9 * G::PLANE];
+    __shared__ T sFx[2][9 * G::NFX];
+    __shared__ T sFy[2][9 * G::NFY];
 
     const int t = threadIdx.x;
     const int tx = t % TX, ty = t / TX;
@@ -736,13 +706,14 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2)))
     }
 
     // Staging of plane k into buffer pb: the own cell (own: its value from the
-    // window) and the halo cell (hv: loaded ahead with a float cache).
+    // window) and the halo cell (hv: loaded ahead).
     T hv[9];
     auto halo_load = [&](int k) {
         if (hslot >= 0) {
+            const Args K = kernel_args<Args>();
 #pragma unroll
             for (int v = 0; v < 9; ++v)
-                hv[v] = Pc[v * d.sv + hoff + (long long)k * st];
+                hv[v] = K.Pc[v * K.d.sv + hoff + (long long)k * st];
         }
     };
     auto stage = [&](int k, int pb, const T* own, bool hv_loaded) {
@@ -752,10 +723,11 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2)))
             for (int v = 0; v < 9; ++v)
                 P[v * G::PLANE + oslot] = own[v];
         } else if (own_ghost) {
+            const Args K = kernel_args<Args>();
             const long long o = col + (long long)k * st;
 #pragma unroll
             for (int v = 0; v < 9; ++v)
-                P[v * G::PLANE + oslot] = Pc[v * d.sv + o];
+                P[v * G::PLANE + oslot] = K.Pc[v * K.d.sv + o];
         }
         if (hslot >= 0) {
             if (!hv_loaded)
@@ -772,6 +744,8 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2)))
     // row and column.  One face solver serves both axes (a loop, not
     // unrolled, keeps one copy of its code).
     auto faces = [&](int k, int pb, int fb) {
+        const Args K = kernel_args<Args>();
+        const Dev& d = K.d;
         const double zc = d.lo[2] + (k + 0.5) * d.dx[2];
         const int ntask = t >= G::NT - 64 ? 3 : 2;
 #pragma nounroll
@@ -800,25 +774,24 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
     // The update of plane k (x and y fluxes in face buffer fb): the z face
     // above the cell from the window (which moves up one plane), the flux
-    // differences, sources, RK combination and recovery.  With a float
-    // cache the stage inputs are loaded first, so that the z face covers
-    // their latency, and the halo cell of plane kh is loaded before the
-    // recovery; a double cache has no registers to spare for either.
+    // differences, sources, RK combination and recovery.  The stage inputs
+    // are loaded first, so that the z face covers their latency, and the halo
+    // cell of plane kh is loaded before the recovery.
     auto update = [&](int k, int fb, int kh) {
-        constexpr bool early = sizeof(T) < sizeof(double);
         if (!act) {
-            if (early && kh >= 0)
+            if (kh >= 0)
                 halo_load(kh);
             return;
         }
+        const Args K = kernel_args<Args>();
+        const Dev& d = K.d;
         const long long c = i + (long long)nx * (j + (long long)ny * k);
         double un[9], us[9];
-        if constexpr (early)
-            stage_load<NT>(d, Un, Us, c, un, us);
+        stage_load<NT>(d, K.Un, K.Us, c, un, us);
         T qd[9];
 #pragma unroll
         for (int v = 0; v < 9; ++v)
-            qd[v] = Pc[v * d.sv + col + (long long)(k + 2) * st];
+            qd[v] = K.Pc[v * d.sv + col + (long long)(k + 2) * st];
         T q[9], qL[9], qR[9], Fc[9];
 #pragma unroll
         for (int v = 0; v < 9; ++v) {
@@ -833,8 +806,6 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2)))
         const double zc = d.lo[2] + (k + 0.5) * d.dx[2];
         face_flux<2, KIND>(qL, qR, x, y, zc + 0.5 * d.dx[2], i + (long long)nx * (j + (long long)ny * (k + 1)), d,
                            Fc);
-        if constexpr (!early)
-            stage_load<NT>(d, Un, Us, c, un, us);
         double R[9];
 #pragma unroll
         for (int v = 0; v < 9; ++v) {
@@ -854,44 +825,35 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2)))
         }
         Geo g;
         add_sources<KIND>(d, x, y, zc, c, q, g, R);
-        if (early && kh >= 0)
+        if (kh >= 0)
             halo_load(kh);
         int iters = 0;
-        int flags = stage_finish<NT>(d, g, R, q, un, us, Uout, c, Pn, col + (long long)k * st, i, j, k, dt, a, b,
-                                     fout, iters);
+        const Args L = kernel_args<Args>();
+        int flags = stage_finish<NT>(L.d, g, R, q, un, us, L.Uout, c, L.Pn, col + (long long)k * st, i, j, k, L.dt, L.a,
+                                     L.b, L.fout, iters);
         tally(flags, iters, nfail, natm, npf, nfb, itmax);
     };
 
-    if constexpr (DB) {
-        // prologue: planes k0 and k0 + 1 staged, the faces of k0 solved
-        stage(k0, 0, qb, false);
+    // prologue: planes k0 and k0 + 1 staged, the faces of k0 solved
+    stage(k0, 0, qb, false);
+    __syncthreads();
+    faces(k0, 0, 0);
+    if (k0 + 1 < k1)
+        stage(k0 + 1, 1, qc, false);
+    __syncthreads();
+    // plane k: the faces of k + 1, the update of k, the staging of k + 2 (into
+    // the buffer plane k used; its own cell is the window's qc once the update
+    // has moved the window up)
+    for (int k = k0; k < k1; ++k) {
+        const int cur = (k - k0) & 1, nxt = cur ^ 1;
+        if (k + 1 < k1)
+            faces(k + 1, nxt, nxt);
+        update(k, cur, k + 2 < k1 ? k + 2 : -1);   // also loads the halo cell of k + 2
+        if (k + 2 < k1)
+            stage(k + 2, cur, qc, true);
         __syncthreads();
-        faces(k0, 0, 0);
-        if (k0 + 1 < k1)
-            stage(k0 + 1, 1, qc, false);
-        __syncthreads();
-        // plane k: the faces of k + 1, the update of k, the staging of k + 2
-        // (into the buffer plane k used; its own cell is the window's qc once
-        // the update has moved the window up)
-        for (int k = k0; k < k1; ++k) {
-            const int cur = (k - k0) & 1, nxt = cur ^ 1;
-            if (k + 1 < k1)
-                faces(k + 1, nxt, nxt);
-            update(k, cur, k + 2 < k1 ? k + 2 : -1);   // also loads the halo cell of k + 2
-            if (k + 2 < k1)
-                stage(k + 2, cur, qc, true);
-            __syncthreads();
-        }
-    } else {
-        for (int k = k0; k < k1; ++k) {
-            stage(k, 0, qb, false);
-            __syncthreads();
-            faces(k, 0, 0);
-            __syncthreads();
-            update(k, 0, -1);
-        }
     }
-    count_sums(cnt, nfail, natm, npf, nfb, itmax);
+    count_sums(kernel_args<Args>().cnt, nfail, natm, npf, nfb, itmax);
 }
 
 template <int KIND, typename T>
@@ -1712,15 +1674,13 @@ static void launch_substep_nt(int kind, const T* Pc, T* Pn, const double* Un, co
     const int ntiles = ntx * nty;
     const long long nseg = (d.n[2] + SEG - 1) / SEG;
     const dim3 grid((unsigned)(ntiles * nseg)), block(TX * TY);
+    const SubstepArgs<T, TS, TO> A{Pc, Pn, Un, Us, Uout, dt, a, b, cnt, fout, ntx, ntiles, d};
     if (kind == FLAT)
-        hipLaunchKernelGGL((k_substep<FLAT, TX, TY, SEG, NT, T, TS, TO>), grid, block, 0, s, Pc, Pn, Un, Us, Uout, d,
-                           dt, a, b, cnt, fout, ntx, ntiles);
+        hipLaunchKernelGGL((k_substep<FLAT, TX, TY, SEG, NT, T, TS, TO>), grid, block, 0, s, A);
     else if (kind == ISO)
-        hipLaunchKernelGGL((k_substep<ISO, TX, TY, SEG, NT, T, TS, TO>), grid, block, 0, s, Pc, Pn, Un, Us, Uout, d,
-                           dt, a, b, cnt, fout, ntx, ntiles);
+        hipLaunchKernelGGL((k_substep<ISO, TX, TY, SEG, NT, T, TS, TO>), grid, block, 0, s, A);
     else
-        hipLaunchKernelGGL((k_substep<STORED, TX, TY, SEG, NT, T, TS, TO>), grid, block, 0, s, Pc, Pn, Un, Us, Uout,
-                           d, dt, a, b, cnt, fout, ntx, ntiles);
+        hipLaunchKernelGGL((k_substep<STORED, TX, TY, SEG, NT, T, TS, TO>), grid, block, 0, s, A);
 }
 
 template <typename T, typename TS, typename TO>
@@ -1923,7 +1883,8 @@ hipError_t launch_batch_evolve(int shape, int lds, size_t lds_bytes, BatchProb* 
     template hipError_t launch_update<T, TS, TO>(int, const T*, const T*, const T*, const T*, T*,       \
                                                  const double*, const TS*, TO*, const Dev&, double,     \
                                                  double, double, unsigned long long*, unsigned char*,   \
-                                                 hipStream_t);                                          \
+                                                 hipStream_t);
+#define GRMHD_INSTANTIATE_SUBSTEP(T, TS, TO)                                                            \
     template hipError_t launch_substep<T, TS, TO>(int, const T*, T*, const double*, const TS*, TO*,     \
                                                   const Dev&, double, double, double, unsigned long long*, \
                                                   unsigned char*, hipStream_t);
@@ -1947,6 +1908,9 @@ GRMHD_INSTANTIATE_UPDATE(double, double, double)
 GRMHD_INSTANTIATE_UPDATE(float, double, float)
 GRMHD_INSTANTIATE_UPDATE(float, float, float)
 GRMHD_INSTANTIATE_UPDATE(float, float, double)
+GRMHD_INSTANTIATE_SUBSTEP(float, double, float)
+GRMHD_INSTANTIATE_SUBSTEP(float, float, float)
+GRMHD_INSTANTIATE_SUBSTEP(float, float, double)
 
 #define GRMHD_INSTANTIATE(T)                                                                            \
     template hipError_t launch_fill<T>(T*, long long, double, hipStream_t);                             \

@@ -1,0 +1,517 @@
+// grmhd_sweep.hip -- one FP64 substep of a grid (or its right-hand side) in one
+// launch, MC or PPM reconstruction.
+//
+// A wave owns 62 consecutive positions of a plane's rows laid end to end (each
+// row with one ghost position at either end) and marches over a segment of
+// planes; lanes 0 and 63 repeat the neighbouring waves' edge positions, so that
+// a wave needs nothing from another one: no barriers, no shared staging.
+//   x  every lane reconstructs its own cell and solves the face on its left; the
+//      left state comes from the lane to the left, the flux through the right
+//      face from the lane to the right (DPP wave shifts);
+//   y  both faces of the cell, from the rows beside it (the caches serve a row
+//      again to the waves of its neighbours);
+//   z  the face above the cell; the flux below, the left state and the next cell
+//      are carried from plane to plane in LDS (each lane its own words).
+// Then sources, Runge-Kutta combination, recovery and the new primitives, which
+// go to another cache with their ghost images.
+//
+// Bound by vector issue (about 2600 instructions a cell and plane, 65 % busy at
+// two waves per SIMD, 213 to 229 registers).  It replaced, for three RK3 steps
+// or as stated: face kernels and an update on 2D grids (500 x 300, five steps: 551
+// to 342 us) and with PPM (128^3, two steps: 3.59 to 2.75 ms), a kernel that
+// staged 32 x 8 tiles in LDS between two barriers a plane on 3D grids (192^3: 9.11
+// to 8.74 ms; 101 x 87 x 75, where tiles are ragged: 1.25 to 0.93 ms; 64^3: even),
+// and nine launches of a right-hand side (24 x 20 x 16: 41 to 11.5 us).  The four
+// faces a cell (one of y twice) cost 12 % more instructions than sharing would;
+// three waves per SIMD spill 30 to 50 registers and are 25 % slower.
+#include "grmhd_cell.h"
+#include "grmhd_device.h"
+#include "grmhd_internal.h"
+
+namespace grmhd {
+
+static constexpr int SWEEP_USED = 62;   // positions a wave updates
+
+// The value of the lane to the left / right (wave-wide shift; the first / last
+// lane gets an unspecified one).
+__device__ __forceinline__ double from_left(double x)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x138, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x138, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+
+__device__ __forceinline__ double from_right(double x)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x130, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x130, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+
+// Memory accesses with a uniform 64-bit base, a 32-bit byte offset per lane and a
+// uniform one: the address arithmetic stays in the scalar unit.  NT: streaming.
+typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const double* base)
+{
+    return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0xffffffffu, 0x00027000);
+}
+
+template <bool NT = false>
+__device__ __forceinline__ double buf_load(const double* base, unsigned lane, unsigned uniform = 0)
+{
+    return __builtin_bit_cast(double,
+                              __builtin_amdgcn_raw_buffer_load_b64(buffer_at(base), lane, uniform, NT ? 2 : 0));
+}
+
+template <bool NT = false>
+__device__ __forceinline__ void buf_store(double* base, unsigned lane, double x)
+{
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2v, x), buffer_at(base), lane, 0, NT ? 2 : 0);
+}
+
+struct SweepKernelArgs {
+    SweepArgs A;
+    Dev d;
+};
+
+__device__ __forceinline__ SweepKernelArgs sweep_args()
+{
+    return kernel_args<SweepKernelArgs>();
+}
+
+// Lower and upper edge values of the middle cell of a line of cells at(-2 .. 2).
+template <bool PPM, typename At>
+__device__ __forceinline__ void cell_edges(At&& at, double& lo, double& hi)
+{
+    if constexpr (PPM) {
+        ppm_edges(at(-2), at(-1), at(0), at(1), at(2), lo, hi);
+    } else {
+        const double c = at(0), h = mc_hslope(at(-1), c, at(1));
+        lo = c - h;
+        hi = c + h;
+    }
+}
+
+// Index c of an axis of n cells mapped into the domain by the boundary rule.
+__device__ __forceinline__ int map_cell(int c, int n, int bc)
+{
+    if (c >= 0 && c < n)
+        return c;
+    if (bc != 0)
+        return c < 0 ? 0 : n - 1;
+    return c < 0 ? c + n : c - n;
+}
+
+// Where the primitives come from: the ghosted cache, or, for a right-hand side,
+// the caller's dense array with indices mapped by the boundary rule.
+template <bool DENSE, int G>
+struct Source {
+    static constexpr int X = G - 1;          // cells read beside one along x
+    unsigned o;                              // the lane's own position
+    unsigned ox[2 * X + 1], oy[2 * G + 1];   // dense: shifted along x, along y
+
+    __device__ __forceinline__ Source(const Dev& d, int i, int j)
+    {
+        if constexpr (DENSE) {
+            const int im = map_cell(i, d.n[0], d.bc[0]);
+            o = (unsigned)(im + d.n[0] * j) * 8u;
+#pragma unroll
+            for (int m = -X; m <= X; ++m)
+                ox[m + X] = d.act[0] ? (unsigned)(map_cell(i + m, d.n[0], d.bc[0]) + d.n[0] * j) * 8u : o;
+#pragma unroll
+            for (int m = -G; m <= G; ++m)
+                oy[m + G] = d.act[1] ? (unsigned)(im + d.n[0] * map_cell(j + m, d.n[1], d.bc[1])) * 8u : o;
+        } else {
+            o = (unsigned)((j + d.g[1]) * d.px + i + d.g[0]) * 8u;
+        }
+    }
+
+    // Variable v of the cell shifted by (x, y, z) (one of them at most not 0) in plane k.
+    __device__ __forceinline__ double at(const SweepArgs& A, const Dev& d, int v, int k, int x, int y, int z) const
+    {
+        if constexpr (DENSE) {
+            const int kk = d.act[2] ? map_cell(k + z, d.n[2], d.bc[2]) : 0;
+            const double* p = A.P + v * d.N + (long long)kk * d.n[0] * d.n[1];
+            return buf_load(p, x != 0 ? ox[x + X] : (y != 0 ? oy[y + G] : o));
+        } else {
+            // shifts count from the lowest cell read, which keeps the offsets positive
+            const double* p = A.Pc + v * d.sv + (long long)(k + d.g[2] + z) * d.px * d.py - X;
+            if (y != 0)
+                return buf_load(p - G * d.px, o + 8u * X, (unsigned)((y + G) * d.px) * 8u);
+            return buf_load(p, o + 8u * (x + X));
+        }
+    }
+};
+
+// Store the new primitives p of a cell (i, j, k) at cache position o of its plane
+// and at the ghost positions whose boundary rule copies it (as store_prim).
+__device__ __forceinline__ void sweep_store(double* Pn, const Dev& d, unsigned o, int i, int j, int k,
+                                            const double* p)
+{
+    const long long st = (long long)d.px * d.py;
+    auto put = [&](int plane, unsigned at) {
+#pragma unroll
+        for (int v = 0; v < 9; ++v)
+            buf_store(Pn + v * d.sv + (plane + d.g[2]) * st, at, p[v]);
+    };
+    put(k, o);
+    auto images = [&](int a, int idx, int n, int g, unsigned step) {
+        if (!d.act[a])
+            return;
+        if (d.bc[a] == 0) {
+            if (idx < g)
+                put(k, o + (unsigned)n * step);
+            if (idx >= n - g)
+                put(k, o - (unsigned)n * step);
+        } else if (idx == 0 || idx == n - 1) {
+            for (int e = 1; e <= g; ++e)
+                put(k, idx == 0 ? o - (unsigned)e * step : o + (unsigned)e * step);
+        }
+    };
+    images(0, i, d.n[0], d.g[0], 8u);
+    images(1, j, d.n[1], d.g[1], 8u * (unsigned)d.px);
+    if (d.act[2]) {
+        const int n = d.n[2], g = d.g[2];
+        if (d.bc[2] == 0) {
+            if (k < g)
+                put(k + n, o);
+            if (k >= n - g)
+                put(k - n, o);
+        } else if (k == 0 || k == n - 1) {
+            for (int e = 1; e <= g; ++e)
+                put(k == 0 ? -e : k + e, o);
+        }
+    }
+}
+
+enum { SWEEP_STEP = 0, SWEEP_RHS = 1 };
+
+template <int KIND, bool PPM, int ROLE>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_sweep(SweepKernelArgs)
+{
+    constexpr int G = PPM ? 3 : 2, X = G - 1;
+    // carried along z: the left state and the flux of the next face, the next cell
+    // (and for PPM the cell below)
+    __shared__ double sL[9 * 64], sF[9 * 64], sQ[9 * 64], sM[PPM ? 9 * 64 : 1];
+
+    const SweepKernelArgs K0 = sweep_args();
+    const SweepArgs& A0 = K0.A;
+    // items (row group, segment), the row group fastest, in contiguous runs per XCD
+    const unsigned run = gridDim.x / 8;
+    const unsigned item = (blockIdx.x % 8) * run + blockIdx.x / 8;
+    if (item >= (unsigned)A0.ngrp * (unsigned)A0.nseg)
+        return;
+    const int seg = (int)(item / (unsigned)A0.ngrp), grp = (int)(item - (unsigned)seg * (unsigned)A0.ngrp);
+    const int lane = threadIdx.x;
+    const int nx = K0.d.n[0], ny = K0.d.n[1];
+    const bool ax = K0.d.act[0], ay = K0.d.act[1], az = K0.d.act[2];
+    const int wx = ax ? nx + 2 : nx;
+    const int s = grp * SWEEP_USED + lane - 1, total = ny * wx;
+    const int sc = min(max(s, 0), total - 1);
+    const int j = sc / wx, i = sc - j * wx - (ax ? 1 : 0);
+    const bool own = s == sc && lane >= 1 && lane <= SWEEP_USED && i >= 0 && i < nx;
+    const int k0 = seg * A0.seg, k1 = min(k0 + A0.seg, K0.d.n[2]);
+    const int ic = min(max(i, 0), nx - 1);   // a cell of the row, also for the lanes at its ends
+    const unsigned oc = (unsigned)(ic + nx * j) * 8u;
+    const Source<ROLE == SWEEP_RHS, G> P(K0.d, i, j);
+
+    double q0[9];
+#pragma unroll
+    for (int v = 0; v < 9; ++v)
+        q0[v] = P.at(A0, K0.d, v, k0, 0, 0, 0);
+    if (az) {
+        const Dev& d = K0.d;
+        double qL[9], qR[9], F[9];
+#pragma unroll
+        for (int v = 0; v < 9; ++v) {
+            double q[2 * G + 1], e, hi;   // planes k0 - G .. k0 + G
+#pragma unroll
+            for (int m = -G; m < G; ++m)
+                q[m + G] = m == 0 ? q0[v] : P.at(A0, d, v, k0, 0, 0, m);
+            cell_edges<PPM>([&](int m) { return q[m - 1 + G]; }, e, qL[v]);
+            cell_edges<PPM>([&](int m) { return q[m + G]; }, qR[v], hi);
+            sL[v * 64 + lane] = hi;
+            sQ[v * 64 + lane] = q[1 + G];
+            if (PPM)
+                sM[v * 64 + lane] = q[-1 + G];
+        }
+        const Geo g = face_geo<2, KIND>(d, d.lo[0] + (i + 0.5) * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1],
+                                        d.lo[2] + k0 * d.dx[2], ic + (long long)nx * (j + (long long)ny * k0));
+        face_solve64<2>(qL, qR, geo_cast<double>(g), d, F);
+#pragma unroll
+        for (int v = 0; v < 9; ++v)
+            sF[v * 64 + lane] = F[v];
+    }
+    int nfail = 0, natm = 0, npf = 0, nfb = 0, itmax = 0;
+
+    // The loads of a plane go out in groups (left to itself the compiler loads a
+    // variable's stencil, waits and loads the next: 40 exposed latencies a plane,
+    // and 1.6 ms instead of 1.0 ms for a 192^3 substep).
+    for (int k = k0; k < k1; ++k) {
+        double R[9];
+#pragma unroll
+        for (int v = 0; v < 9; ++v)
+            R[v] = 0.0;
+        if (ay) {
+            const SweepKernelArgs K = sweep_args();
+            const Dev& d = K.d;
+            double lL[9], lR[9], hL[9], hR[9], Fl[9], Fh[9];
+            // PPM: in three batches of variables, which bounds the registers
+            constexpr int NB = PPM ? 3 : 9;
+#pragma unroll
+            for (int b = 0; b < 9; b += NB) {
+                double r[NB][2 * G + 1];
+#pragma unroll
+                for (int v = 0; v < NB; ++v)
+#pragma unroll
+                    for (int m = -G; m <= G; ++m)
+                        r[v][m + G] = m == 0 ? q0[b + v] : P.at(K.A, d, b + v, k, 0, m, 0);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int v = 0; v < NB; ++v) {
+                    double e;
+                    cell_edges<PPM>([&](int m) { return r[v][m - 1 + G]; }, e, lL[b + v]);
+                    cell_edges<PPM>([&](int m) { return r[v][m + G]; }, lR[b + v], hL[b + v]);
+                    cell_edges<PPM>([&](int m) { return r[v][m + 1 + G]; }, hR[b + v], e);
+                }
+            }
+            const double x = d.lo[0] + (i + 0.5) * d.dx[0], z = d.lo[2] + (k + 0.5) * d.dx[2];
+            const long long f = ic + (long long)nx * (j + (long long)(ny + 1) * k);
+            face_solve64<1>(lL, lR, geo_cast<double>(face_geo<1, KIND>(d, x, d.lo[1] + j * d.dx[1], z, f)), d, Fl);
+            face_solve64<1>(hL, hR, geo_cast<double>(face_geo<1, KIND>(d, x, d.lo[1] + (j + 1) * d.dx[1], z, f + nx)),
+                            d, Fh);
+#pragma unroll
+            for (int v = 0; v < 9; ++v)
+                R[v] = -(Fh[v] - Fl[v]) * d.idx[1];
+        }
+        double q2[9], q3[9];
+        if (ax) {
+            const SweepKernelArgs K = sweep_args();
+            const Dev& d = K.d;
+            double r[9][2 * X + 1], qL[9], qR[9], F[9];
+#pragma unroll
+            for (int v = 0; v < 9; ++v)
+#pragma unroll
+                for (int m = -X; m <= X; ++m)
+                    r[v][m + X] = m == 0 ? q0[v] : P.at(K.A, d, v, k, m, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int v = 0; v < 9; ++v) {
+                double hi;
+                cell_edges<PPM>([&](int m) { return r[v][m + X]; }, qR[v], hi);
+                qL[v] = from_left(hi);
+            }
+            if (!PPM && az) {
+#pragma unroll
+                for (int v = 0; v < 9; ++v)
+                    q2[v] = P.at(K.A, d, v, k, 0, 0, 2);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const long long f = max(i, 0) + (long long)(nx + 1) * (j + (long long)ny * k);
+            const GeoT<double> g = geo_cast<double>(face_geo<0, KIND>(
+                d, d.lo[0] + i * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1], d.lo[2] + (k + 0.5) * d.dx[2], f));
+            if (ay || az)
+                face_solve64<0>(qL, qR, g, d, F);
+            else
+                face_solve<0>(qL, qR, g, d, F);   // 1D grids: the plain order of operations
+#pragma unroll
+            for (int v = 0; v < 9; ++v)
+                R[v] -= (from_right(F[v]) - F[v]) * d.idx[0];
+        }
+        double q[9];
+#pragma unroll
+        for (int v = 0; v < 9; ++v)
+            q[v] = q0[v];
+        if (az) {
+            const SweepKernelArgs K = sweep_args();
+            const Dev& d = K.d;
+            double qL[9], qR[9], F[9];
+            if (PPM || !ax) {
+#pragma unroll
+                for (int v = 0; v < 9; ++v) {
+                    q2[v] = P.at(K.A, d, v, k, 0, 0, 2);
+                    q3[v] = PPM ? P.at(K.A, d, v, k, 0, 0, 3) : 0.0;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int v = 0; v < 9; ++v) {
+                double hi;
+                const double q1 = sQ[v * 64 + lane], qm = PPM ? sM[v * 64 + lane] : 0.0;
+                cell_edges<PPM>(
+                    [&](int m) {
+                        return m == -2 ? qm : (m == -1 ? q[v] : (m == 0 ? q1 : (m == 1 ? q2[v] : q3[v])));
+                    },
+                    qR[v], hi);
+                qL[v] = sL[v * 64 + lane];
+                sL[v * 64 + lane] = hi;
+                if (PPM)
+                    sM[v * 64 + lane] = q[v];
+                q0[v] = q1;
+                sQ[v * 64 + lane] = q2[v];
+            }
+            const GeoT<double> g = geo_cast<double>(
+                face_geo<2, KIND>(d, d.lo[0] + (i + 0.5) * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1],
+                                  d.lo[2] + (k + 1) * d.dx[2], ic + (long long)nx * (j + (long long)ny * (k + 1))));
+            face_solve64<2>(qL, qR, g, d, F);
+#pragma unroll
+            for (int v = 0; v < 9; ++v) {
+                R[v] -= (F[v] - sF[v * 64 + lane]) * d.idx[2];
+                sF[v * 64 + lane] = F[v];
+            }
+        }
+        const SweepKernelArgs K = sweep_args();
+        const Dev& d = K.d;
+        const SweepArgs& A = K.A;
+        const long long plane = (long long)nx * ny * k;   // uniform
+        double un[9], us[9];
+        // U^n, U^s and U^(s+1) are touched once per cell and substep: past the
+        // last-level cache's size streaming accesses keep them from displacing the
+        // primitives that neighbouring waves read again
+        if constexpr (ROLE == SWEEP_STEP) {
+            if (d.nt) {
+#pragma unroll
+                for (int v = 0; v < 9; ++v)
+                    un[v] = buf_load<true>(A.Un + v * d.N + plane, oc);
+                if (A.Us) {
+#pragma unroll
+                    for (int v = 0; v < 9; ++v)
+                        us[v] = buf_load<true>(A.Us + v * d.N + plane, oc);
+                }
+            } else {
+#pragma unroll
+                for (int v = 0; v < 9; ++v)
+                    un[v] = buf_load(A.Un + v * d.N + plane, oc);
+                if (A.Us) {
+#pragma unroll
+                    for (int v = 0; v < 9; ++v)
+                        us[v] = buf_load(A.Us + v * d.N + plane, oc);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        Geo g;
+        add_sources<KIND>(d, d.lo[0] + (i + 0.5) * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1],
+                          d.lo[2] + (k + 0.5) * d.dx[2], plane + oc / 8u, q, g, R);
+        if constexpr (ROLE == SWEEP_RHS) {
+            if (own) {
+#pragma unroll
+                for (int v = 0; v < 9; ++v)
+                    buf_store(A.R + v * d.N + plane, oc, R[v]);
+                if (A.Pn)
+                    sweep_store(A.Pn, d, (unsigned)((j + d.g[1]) * d.px + i + d.g[0]) * 8u, i, j, k, q);
+            }
+        } else {
+            double u[9], p[9];
+#pragma unroll
+            for (int v = 0; v < 9; ++v) {
+                const double ub = A.Us ? us[v] : un[v];
+                u[v] = ub + A.a * (un[v] - ub) + A.b * (A.dt * R[v]);
+            }
+            int flags = 0, iters = 0;
+            if (own) {
+                flags = recover_cell(d, g, u, q, p, iters);
+                const SweepKernelArgs K2 = sweep_args();
+                const SweepArgs& B = K2.A;
+                const Dev& e = K2.d;
+                if (e.nt) {
+#pragma unroll
+                    for (int v = 0; v < 9; ++v)
+                        buf_store<true>(B.Uo + v * e.N + plane, oc, u[v]);
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 9; ++v)
+                        buf_store(B.Uo + v * e.N + plane, oc, u[v]);
+                }
+                sweep_store(B.Pn, e, P.o, i, j, k, p);
+                if (B.fout)
+                    B.fout[plane + oc / 8u] = (unsigned char)flags;
+            }
+            if (__any(flags != 0)) {
+                nfail += __popcll(__ballot(flags & FLAG_FAIL));
+                natm += __popcll(__ballot(flags & FLAG_ATM));
+                npf += __popcll(__ballot(flags & FLAG_PFLOOR));
+                nfb += __popcll(__ballot(flags & FLAG_FALLBACK));
+            }
+            itmax = max(itmax, iters);
+        }
+    }
+    if constexpr (ROLE == SWEEP_STEP) {
+        for (int m = 32; m > 0; m >>= 1)
+            itmax = max(itmax, __shfl_xor(itmax, m));
+        if (lane == 0) {
+            unsigned long long* cnt = A0.cnt + (size_t)(blockIdx.x % CNT_SLOTS) * CNT_WORDS;
+            if (nfail)
+                atomicAdd(&cnt[CNT_FAIL], (unsigned long long)nfail);
+            if (natm)
+                atomicAdd(&cnt[CNT_ATM], (unsigned long long)natm);
+            if (npf)
+                atomicAdd(&cnt[CNT_PFLOOR], (unsigned long long)npf);
+            if (nfb)
+                atomicAdd(&cnt[CNT_FALLBACK], (unsigned long long)nfb);
+            atomicMax(&cnt[CNT_MAXIT], (unsigned long long)itmax);
+        }
+    }
+}
+
+// Planes per wave: a wave's planes and its first face and loads (half a plane)
+// times the waves, and a tail of unevenly finished work worth 1280 waves (of the
+// 2048 that are resident).  The line lies where measured: 64^3 (4416, 2208, 1518
+// waves) 43.2, 46.8, 44.5 us a substep with 1, 2, 3 planes, 96 x 80 x 72 87, 86,
+// 84, 98, 86, 93 us with 1 to 6, 192^3 0.917, 0.920, 0.933, 0.952 ms with 8, 12,
+// 16, 32.
+static int sweep_segment(long long ngrp, int nz)
+{
+    int best = 1;
+    double cost = 0.0;
+    for (int seg = 1; seg <= nz && seg <= 64; ++seg) {
+        const double c = (double)(ngrp * ((nz + seg - 1) / seg) + 1280) * (seg + 0.5);
+        if (seg == 1 || c < cost) {
+            cost = c;
+            best = seg;
+        }
+    }
+    return best;
+}
+
+template <int ROLE>
+static hipError_t launch_sweep_r(int kind, const SweepArgs& A, const Dev& d, hipStream_t s)
+{
+    const long long wx = d.act[0] ? d.n[0] + 2 : d.n[0];
+    const long long total = wx * d.n[1];
+    // byte offsets within a plane are 32-bit (a plane beyond that would need more
+    // than the card's memory for three caches)
+    if ((long long)d.px * d.py * 8 >= (1LL << 32) || total >= (1LL << 31) - 64)
+        return hipErrorInvalidValue;
+    SweepKernelArgs K{A, d};
+    const long long ngrp = (total + SWEEP_USED - 1) / SWEEP_USED;
+    K.A.ngrp = (int)ngrp;
+    K.A.seg = d.act[2] ? sweep_segment(ngrp, d.n[2]) : 1;
+    K.A.nseg = (d.n[2] + K.A.seg - 1) / K.A.seg;
+    const long long items = ngrp * K.A.nseg, blocks = (items + 7) / 8 * 8;
+    if (blocks >= (1LL << 31))
+        return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks), block(64);
+#define GRMHD_SWEEP(KIND)                                                            \
+    if (d.ppm)                                                                       \
+        hipLaunchKernelGGL((k_sweep<KIND, true, ROLE>), grid, block, 0, s, K);       \
+    else                                                                             \
+        hipLaunchKernelGGL((k_sweep<KIND, false, ROLE>), grid, block, 0, s, K);
+    if (kind == FLAT) {
+        GRMHD_SWEEP(FLAT)
+    } else if (kind == ISO) {
+        GRMHD_SWEEP(ISO)
+    } else {
+        GRMHD_SWEEP(STORED)
+    }
+#undef GRMHD_SWEEP
+    return hipGetLastError();
+}
+
+hipError_t launch_sweep(int kind, const SweepArgs& A, const Dev& d, hipStream_t s)
+{
+    return A.R ? launch_sweep_r<SWEEP_RHS>(kind, A, d, s) : launch_sweep_r<SWEEP_STEP>(kind, A, d, s);
+}
+
+}  // namespace grmhd
