@@ -319,13 +319,28 @@ bool edge_values(const grmhd_ctx* c)
     return c->d.ct && c->d.act[0] + c->d.act[1] + c->d.act[2] > 1;
 }
 
-// Which kernels a substep takes: in FP64 without edge values k_sweep (one
-// launch); mixed precision on 3D grids with MC and cleaning k_substep (one
-// launch); else the face kernels and the update.
+// Which kernels a substep takes: in FP64 k_sweep; mixed precision on 3D grids
+// with MC and cleaning k_substep; else the face kernels and the update.
 template <typename T>
-bool sweeps(const grmhd_ctx* c)
+constexpr bool sweeps()
 {
-    return sizeof(T) == sizeof(double) && !edge_values(c);
+    return sizeof(T) == sizeof(double);
+}
+
+// The scratch of a flux-CT sweep: the face records, whose mass, energy and
+// momentum rows along one active axis hold those parts of the right-hand side,
+// and whose normal-field row there the field along an inactive axis.
+void edge_scratch(const grmhd_ctx* c, grmhd::SweepArgs& A)
+{
+    if (!edge_values(c))
+        return;
+    for (int a = 0; a < 3; ++a) {
+        A.F[a] = (double*)c->F[a];
+        if (c->d.act[a]) {
+            A.R5 = A.F[a];
+            A.Ri = A.F[a] + (5 + a) * c->L.nf[a];
+        }
+    }
 }
 
 template <typename T>
@@ -359,21 +374,23 @@ int fluxes(grmhd_ctx* c, int b, int ndir)
             return rc;
         c->ghosts_ok[b] = true;
     }
-    for (int dir = 0; dir < ndir; ++dir) {
-        if (!c->d.act[dir])
-            continue;
-        rc = timed(c, GRMHD_K_FLUX_X + dir, [&] {
-            return grmhd::launch_flux(c->kind, dir, (const T*)P, faces<T>(c, dir), c->d, c->stream);
-        });
-        if (rc)
-            return rc;
-    }
-    if (edge_values(c) && ndir == 3) {
-        T* F[3] = {faces<T>(c, 0), faces<T>(c, 1), faces<T>(c, 2)};
-        T* W[3] = {(T*)c->W[0], (T*)c->W[1], (T*)c->W[2]};
-        rc = timed(c, GRMHD_K_CT, [&] { return grmhd::launch_ct(F, W, c->d, c->stream); });
-        if (rc)
-            return rc;
+    if constexpr (!sweeps<T>()) {
+        for (int dir = 0; dir < ndir; ++dir) {
+            if (!c->d.act[dir])
+                continue;
+            rc = timed(c, GRMHD_K_FLUX_X + dir, [&] {
+                return grmhd::launch_flux(c->kind, dir, (const T*)P, faces<T>(c, dir), c->d, c->stream);
+            });
+            if (rc)
+                return rc;
+        }
+        if (edge_values(c) && ndir == 3) {
+            T* F[3] = {faces<T>(c, 0), faces<T>(c, 1), faces<T>(c, 2)};
+            T* W[3] = {(T*)c->W[0], (T*)c->W[1], (T*)c->W[2]};
+            rc = timed(c, GRMHD_K_CT, [&] { return grmhd::launch_ct(F, W, c->d, c->stream); });
+            if (rc)
+                return rc;
+        }
     }
     return GRMHD_OK;
 }
@@ -414,35 +431,37 @@ int prim_t(grmhd_ctx* c, const double* U, double* P)
 template <typename T>
 int rhs_t(grmhd_ctx* c, const double* P, double* R, bool keep = true)
 {
-    int rc = keep || !sweeps<T>(c) ? prepare_t<T>(c) : GRMHD_OK;
+    int rc = keep || !sweeps<T>() ? prepare_t<T>(c) : GRMHD_OK;
     if (rc)
         return rc;
-    if (sweeps<T>(c)) {
+    if constexpr (sweeps<T>()) {
         grmhd::SweepArgs A{};
         A.P = P;
         A.R = R;
         A.Pn = keep ? cache<double>(c) : nullptr;
+        edge_scratch(c, A);
         rc = timed(c, GRMHD_K_RHS, [&] { return grmhd::launch_sweep(c->kind, A, c->d, c->stream); });
         if (rc)
             return rc;
         c->cache_valid = true;
         c->ghosts_ok[0] = true;
         return GRMHD_OK;
+    } else {
+        rc = timed(c, GRMHD_K_CONS, [&] {
+            return grmhd::launch_cons(c->kind, P, (double*)nullptr, cache<T>(c), c->d, c->stream);
+        });
+        if (rc)
+            return rc;
+        c->cache_valid = true;
+        c->ghosts_ok[0] = true;
+        rc = fluxes<T>(c, 0, 3);
+        if (rc)
+            return rc;
+        return timed(c, GRMHD_K_RHS, [&] {
+            return grmhd::launch_rhs(c->kind, (const T*)faces<T>(c, 0), (const T*)faces<T>(c, 1),
+                                     (const T*)faces<T>(c, 2), (const T*)cache<T>(c), R, c->d, c->stream);
+        });
     }
-    rc = timed(c, GRMHD_K_CONS, [&] {
-        return grmhd::launch_cons(c->kind, P, (double*)nullptr, cache<T>(c), c->d, c->stream);
-    });
-    if (rc)
-        return rc;
-    c->cache_valid = true;
-    c->ghosts_ok[0] = true;
-    rc = fluxes<T>(c, 0, 3);
-    if (rc)
-        return rc;
-    return timed(c, GRMHD_K_RHS, [&] {
-        return grmhd::launch_rhs(c->kind, (const T*)faces<T>(c, 0), (const T*)faces<T>(c, 1),
-                                 (const T*)faces<T>(c, 2), (const T*)cache<T>(c), R, c->d, c->stream);
-    });
 }
 
 // SSP Runge-Kutta stages: U^(s+1) = U^s + a_s (U^n - U^s) + b_s dt R(P^s)
@@ -451,7 +470,7 @@ const double RK3B[3] = {1.0, 0.25, 2.0 / 3.0};
 const double RK2A[2] = {0.0, 0.5};
 const double RK2B[2] = {1.0, 0.5};
 
-// One FP64 substep in one launch: the primitives Pc to Pn, the stage state Us
+// One FP64 substep: the primitives Pc to Pn, the stage state Us
 // (null: U^n) to Uo.
 int sweep_stage(grmhd_ctx* c, const double* Pc, double* Pn, const double* Un, const double* Us, double* Uo, double dt,
                 double a, double b, unsigned char* fout)
@@ -462,6 +481,7 @@ int sweep_stage(grmhd_ctx* c, const double* Pc, double* Pn, const double* Un, co
     A.Un = Un;
     A.Us = Us;
     A.Uo = Uo;
+    edge_scratch(c, A);
     A.cnt = c->cnt;
     A.fout = fout;
     A.dt = dt;
@@ -477,10 +497,9 @@ int update_stage(grmhd_ctx* c, int src, int dst, const double* U, const TS* Us, 
                  double b)
 {
     return timed(c, GRMHD_K_UPDATE, [&] {
-        if constexpr (sizeof(T) < sizeof(double))
-            if (fused<T>(c))
-                return grmhd::launch_substep(c->kind, (const T*)cache<T>(c, src), cache<T>(c, dst), U, Us, Uout, c->d,
-                                             dt, a, b, c->cnt, (unsigned char*)nullptr, c->stream);
+        if (fused<T>(c))
+            return grmhd::launch_substep(c->kind, (const T*)cache<T>(c, src), cache<T>(c, dst), U, Us, Uout, c->d, dt,
+                                         a, b, c->cnt, (unsigned char*)nullptr, c->stream);
         return grmhd::launch_update(c->kind, (const T*)faces<T>(c, 0), (const T*)faces<T>(c, 1),
                                     (const T*)faces<T>(c, 2), (const T*)cache<T>(c, src), cache<T>(c, dst), U, Us,
                                     Uout, c->d, dt, a, b, c->cnt, (unsigned char*)nullptr, c->stream);
@@ -498,7 +517,7 @@ int step_t(grmhd_ctx* c, double* U, double dt)
     // (for flux-CT with the face fluxes corrected in between).  The first stage
     // reads U^n as its stage state; the intermediate stage state has the cache
     // type (float in the mixed path); the last stage writes U.
-    const bool rotate = sweeps<T>(c) || fused<T>(c);
+    const bool rotate = sweeps<T>() || fused<T>(c);
     T* Us = (T*)c->Us;
     for (int s = 0; s < ns; ++s) {
         const bool first = s == 0, last = s == ns - 1;
@@ -507,15 +526,17 @@ int step_t(grmhd_ctx* c, double* U, double dt)
         int rc = fluxes<T>(c, src, rotate ? 0 : 3);
         if (rc)
             return rc;
-        if (sweeps<T>(c))
-            rc = sweep_stage(c, cache<double>(c, src), cache<double>(c, dst), U, first ? nullptr : (double*)Us,
-                             last ? U : (double*)Us, dt, A[s], B[s], nullptr);
-        else if (first)
-            rc = update_stage<T>(c, src, dst, U, (const double*)U, Us, dt, A[s], B[s]);
-        else if (!last)
-            rc = update_stage<T>(c, src, dst, U, (const T*)Us, Us, dt, A[s], B[s]);
-        else
-            rc = update_stage<T>(c, src, dst, U, (const T*)Us, U, dt, A[s], B[s]);
+        if constexpr (sweeps<T>()) {
+            rc = sweep_stage(c, cache<double>(c, src), cache<double>(c, dst), U, first ? nullptr : Us, last ? U : Us, dt,
+                             A[s], B[s], nullptr);
+        } else {
+            if (first)
+                rc = update_stage<T>(c, src, dst, U, (const double*)U, Us, dt, A[s], B[s]);
+            else if (!last)
+                rc = update_stage<T>(c, src, dst, U, (const T*)Us, Us, dt, A[s], B[s]);
+            else
+                rc = update_stage<T>(c, src, dst, U, (const T*)Us, U, dt, A[s], B[s]);
+        }
         if (rc)
             return rc;
         c->ghosts_ok[dst] = true;

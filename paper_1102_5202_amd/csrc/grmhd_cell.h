@@ -2,6 +2,7 @@
 #pragma once
 
 #include "grmhd_device.h"
+#include "grmhd_internal.h"
 
 namespace grmhd {
 
@@ -65,6 +66,43 @@ __device__ __forceinline__ void store_prim(const Dev& d, T* __restrict__ P, long
                     P[v * d.sv + pc + e * s1] = (T)p[v];
         }
     }
+}
+
+// Per-thread counts reduced over the wave, one atomic per wave and counter
+// into the block's slot (never a returning atomic: waiting on one would also
+// wait for the wave's outstanding stores).
+__device__ __forceinline__ void count_sums(unsigned long long* cnt_base, int nf, int na, int np,
+                                           int nb, int itmax)
+{
+    unsigned long long* cnt = cnt_base + (size_t)(blockIdx.x % CNT_SLOTS) * CNT_WORDS;
+    for (int o = 32; o > 0; o >>= 1) {
+        nf += __shfl_xor(nf, o);
+        na += __shfl_xor(na, o);
+        np += __shfl_xor(np, o);
+        nb += __shfl_xor(nb, o);
+        itmax = max(itmax, __shfl_xor(itmax, o));
+    }
+    unsigned long long act = __ballot(1);
+    if (__lane_id() == __ffsll((long long)act) - 1) {
+        if (nf)
+            atomicAdd(&cnt[CNT_FAIL], (unsigned long long)nf);
+        if (na)
+            atomicAdd(&cnt[CNT_ATM], (unsigned long long)na);
+        if (np)
+            atomicAdd(&cnt[CNT_PFLOOR], (unsigned long long)np);
+        if (nb)
+            atomicAdd(&cnt[CNT_FALLBACK], (unsigned long long)nb);
+        atomicMax(&cnt[CNT_MAXIT], (unsigned long long)itmax);
+    }
+}
+
+__device__ __forceinline__ void tally(int flags, int iters, int& nf, int& na, int& np, int& nb, int& itmax)
+{
+    nf += (flags & FLAG_FAIL) != 0;
+    na += (flags & FLAG_ATM) != 0;
+    np += (flags & FLAG_PFLOOR) != 0;
+    nb += (flags & FLAG_FALLBACK) != 0;
+    itmax = max(itmax, iters);
 }
 
 }  // namespace grmhd

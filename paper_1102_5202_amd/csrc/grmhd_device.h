@@ -506,16 +506,11 @@ __device__ __forceinline__ void face_solve_t(T* qL, T* qR, const GeoT<T>& g, con
 }
 
 // The face solver at face f of axis D (position x, y, z) with the metric there.
-// PLAIN: face_solve in FP64 too.
-template <int D, int KIND, bool PLAIN = false, typename T>
+template <int D, int KIND, typename T>
 __device__ __forceinline__ void face_flux(T* qL, T* qR, double x, double y, double z, long long f,
                                           const Dev& d, T* Fo)
 {
-    const GeoT<T> g = geo_cast<T>(face_geo<D, KIND>(d, x, y, z, f));
-    if constexpr (PLAIN)
-        face_solve<D>(qL, qR, g, d, Fo);
-    else
-        face_solve_t<D>(qL, qR, g, d, Fo);
+    face_solve_t<D>(qL, qR, geo_cast<T>(face_geo<D, KIND>(d, x, y, z, f)), d, Fo);
 }
 
 

@@ -50,8 +50,8 @@ template <typename T, typename TS, typename TO>
 hipError_t launch_substep(int kind, const T* Pc, T* Pn, const double* Un, const TS* Us, TO* Uout, const Dev& d,
                           double dt, double a, double b, unsigned long long* cnt, unsigned char* fout,
                           hipStream_t s);
-// One FP64 substep, or one right-hand side (R set), of a grid in one launch
-// (grmhd_sweep.hip).
+// One FP64 substep, or one right-hand side (R set), of a grid: one launch, two
+// for flux-CT with edge values (grmhd_sweep.hip).
 struct SweepArgs {
     const double* Pc;   // substep: the primitives (ghosted cache)
     const double* P;    // right-hand side: the caller's primitives (dense)
@@ -60,6 +60,9 @@ struct SweepArgs {
     const double* Us;   // U^s, or null: the first stage's, U^n
     double* Uo;         // U^(s+1)
     double* R;
+    double* R5;           // flux-CT with edge values (else null): [5][N] scratch,
+    double* Ri;           // [N] for the field along an inactive axis, and
+    double* F[3];         // the face records, whose transverse field rows are used
     unsigned long long* cnt;
     unsigned char* fout;   // may be null: per-cell recovery flags
     double dt, a, b;

@@ -8,7 +8,7 @@
 // policy and the status counters.  In FP64 that is one launch of k_sweep
 // (grmhd_sweep.hip).  Here: mixed precision on 3D grids in one launch of
 // k_substep (x and y faces from planes staged in LDS, z faces from a register
-// window); mixed precision on 1D and 2D grids or with PPM, and flux-CT
+// window); mixed precision on 1D and 2D grids, with PPM or with flux-CT
 // (k_ct_edges, k_ct_faces), with face kernels per active axis (k_flux_x,
 // k_flux_march, k_flux_ppm) and the cell kernel k_update.  Every kernel that
 // writes primitives also writes their ghost images, so the ghost pass k_ghosts
@@ -98,12 +98,12 @@ __global__ __launch_bounds__(BLOCK) void k_ghosts(T* __restrict__ Pc, Dev d, lon
         Pc[v * d.sv + dst] = Pc[v * d.sv + sp];
 }
 
-template <int D, int KIND, bool NT, bool PLAIN = false, typename T>
+template <int D, int KIND, bool NT, typename T>
 __device__ __forceinline__ void face_store(T* qL, T* qR, double x, double y, double z, const Dev& d,
                                            T* __restrict__ F, long long NF, long long f)
 {
     T Fo[9];
-    face_flux<D, KIND, PLAIN>(qL, qR, x, y, z, f, d, Fo);
+    face_flux<D, KIND>(qL, qR, x, y, z, f, d, Fo);
     // the face records are read back by another kernel, not by this one: on
     // large grids (NT) nontemporal stores
     if constexpr (NT) {
@@ -139,8 +139,8 @@ __global__ __launch_bounds__(BLOCK) void k_flux_x(const T* __restrict__ Pc, T* _
         qL[v] = q1 + mc_hslope(q0, q1, q2);
         qR[v] = q2 - mc_hslope(q1, q2, q3);
     }
-    face_store<0, KIND, NT, true>(qL, qR, d.lo[0] + i * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1],
-                                  d.lo[2] + (k + 0.5) * d.dx[2], d, F, d.nf[0], f);
+    face_store<0, KIND, NT>(qL, qR, d.lo[0] + i * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1],
+                        d.lo[2] + (k + 0.5) * d.dx[2], d, F, d.nf[0], f);
 }
 
 // y or z faces: a thread marches along D over a segment of up to SEG faces at
@@ -385,43 +385,6 @@ __device__ __forceinline__ void rhs_cell(const Dev& d, const T* __restrict__ Fx,
     }
     add_sources<KIND>(d, d.lo[0] + (i + 0.5) * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1],
                       d.lo[2] + (k + 0.5) * d.dx[2], c, q, g, R);
-}
-
-// Per-thread counts reduced over the wave, one atomic per wave and counter
-// into the block's slot (never a returning atomic: waiting on one would also
-// wait for the wave's outstanding stores).
-__device__ __forceinline__ void count_sums(unsigned long long* cnt_base, int nf, int na, int np,
-                                           int nb, int itmax)
-{
-    unsigned long long* cnt = cnt_base + (size_t)(blockIdx.x % CNT_SLOTS) * CNT_WORDS;
-    for (int o = 32; o > 0; o >>= 1) {
-        nf += __shfl_xor(nf, o);
-        na += __shfl_xor(na, o);
-        np += __shfl_xor(np, o);
-        nb += __shfl_xor(nb, o);
-        itmax = max(itmax, __shfl_xor(itmax, o));
-    }
-    unsigned long long act = __ballot(1);
-    if (__lane_id() == __ffsll((long long)act) - 1) {
-        if (nf)
-            atomicAdd(&cnt[CNT_FAIL], (unsigned long long)nf);
-        if (na)
-            atomicAdd(&cnt[CNT_ATM], (unsigned long long)na);
-        if (np)
-            atomicAdd(&cnt[CNT_PFLOOR], (unsigned long long)np);
-        if (nb)
-            atomicAdd(&cnt[CNT_FALLBACK], (unsigned long long)nb);
-        atomicMax(&cnt[CNT_MAXIT], (unsigned long long)itmax);
-    }
-}
-
-__device__ __forceinline__ void tally(int flags, int iters, int& nf, int& na, int& np, int& nb, int& itmax)
-{
-    nf += (flags & FLAG_FAIL) != 0;
-    na += (flags & FLAG_ATM) != 0;
-    np += (flags & FLAG_PFLOOR) != 0;
-    nb += (flags & FLAG_FALLBACK) != 0;
-    itmax = max(itmax, iters);
 }
 
 // The stage inputs of cell c: U^n and U^s.  U^n, U^s and U^(s+1) are touched
@@ -1904,7 +1867,6 @@ hipError_t launch_batch_evolve(int shape, int lds, size_t lds_bytes, BatchProb* 
                                                hipStream_t);
 GRMHD_INSTANTIATE_BATCH(double)
 GRMHD_INSTANTIATE_BATCH(float)
-GRMHD_INSTANTIATE_UPDATE(double, double, double)
 GRMHD_INSTANTIATE_UPDATE(float, double, float)
 GRMHD_INSTANTIATE_UPDATE(float, float, float)
 GRMHD_INSTANTIATE_UPDATE(float, float, double)
@@ -1915,14 +1877,16 @@ GRMHD_INSTANTIATE_SUBSTEP(float, float, double)
 #define GRMHD_INSTANTIATE(T)                                                                            \
     template hipError_t launch_fill<T>(T*, long long, double, hipStream_t);                             \
     template hipError_t launch_ghosts<T>(T*, const Dev&, hipStream_t);                                  \
-    template hipError_t launch_flux<T>(int, int, const T*, T*, const Dev&, hipStream_t);               \
-    template hipError_t launch_ct<T>(T* const*, T* const*, const Dev&, hipStream_t);                   \
-    template hipError_t launch_rhs<T>(int, const T*, const T*, const T*, const T*, double*, const Dev&,  \
-                                      hipStream_t);                                                     \
     template hipError_t launch_cons<T>(int, const double*, double*, T*, const Dev&, hipStream_t);      \
     template hipError_t launch_prim<T>(int, const double*, double*, T*, const Dev&, unsigned long long*, \
                                        hipStream_t);
 GRMHD_INSTANTIATE(double)
 GRMHD_INSTANTIATE(float)
+
+// mixed precision only
+template hipError_t launch_flux<float>(int, int, const float*, float*, const Dev&, hipStream_t);
+template hipError_t launch_ct<float>(float* const*, float* const*, const Dev&, hipStream_t);
+template hipError_t launch_rhs<float>(int, const float*, const float*, const float*, const float*, double*, const Dev&,
+                                      hipStream_t);
 
 }  // namespace grmhd

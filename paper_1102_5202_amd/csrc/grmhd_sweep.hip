@@ -1,5 +1,5 @@
 // grmhd_sweep.hip -- one FP64 substep of a grid (or its right-hand side) in one
-// launch, MC or PPM reconstruction.
+// launch (two for flux-CT), MC or PPM reconstruction.
 //
 // A wave owns 62 consecutive positions of a plane's rows laid end to end (each
 // row with one ghost position at either end) and marches over a segment of
@@ -13,7 +13,8 @@
 //   z  the face above the cell; the flux below, the left state and the next cell
 //      are carried from plane to plane in LDS (each lane its own words).
 // Then sources, Runge-Kutta combination, recovery and the new primitives, which
-// go to another cache with their ghost images.
+// go to another cache with their ghost images.  Flux-CT leaves the cell to a
+// second launch (k_ct_update).
 //
 // Bound by vector issue (about 2600 instructions a cell and plane, 65 % busy at
 // two waves per SIMD, 213 to 229 registers).  It replaced, for three RK3 steps
@@ -185,9 +186,23 @@ __device__ __forceinline__ void sweep_store(double* Pn, const Dev& d, unsigned o
     }
 }
 
-enum { SWEEP_STEP = 0, SWEEP_RHS = 1 };
+// What a sweep leaves: the new state; the right-hand side; or, for flux-CT, the
+// flux differences and sources of mass, energy and momentum (and the flux
+// differences of the field along an inactive axis, which no edge value corrects)
+// and the transverse field fluxes of every face, which k_ct_update takes further.  DENSE: the
+// primitives come from the caller's array.
+enum { SWEEP_STEP = 0, SWEEP_RHS = 1, SWEEP_CT = 2 };
 
-template <int KIND, bool PPM, int ROLE>
+// The transverse field components of a face's flux along D into its records.
+template <int D>
+__device__ __forceinline__ void put_transverse(double* F, long long nf, long long f, const double* Fo)
+{
+    constexpr int B = D == 0 ? 1 : 0, C = D == 2 ? 1 : 2;
+    F[(5 + B) * nf + f] = Fo[5 + B];
+    F[(5 + C) * nf + f] = Fo[5 + C];
+}
+
+template <int KIND, bool PPM, int ROLE, bool DENSE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_sweep(SweepKernelArgs)
 {
     constexpr int G = PPM ? 3 : 2, X = G - 1;
@@ -210,11 +225,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     const int s = grp * SWEEP_USED + lane - 1, total = ny * wx;
     const int sc = min(max(s, 0), total - 1);
     const int j = sc / wx, i = sc - j * wx - (ax ? 1 : 0);
-    const bool own = s == sc && lane >= 1 && lane <= SWEEP_USED && i >= 0 && i < nx;
+    const bool used = s == sc && lane >= 1 && lane <= SWEEP_USED, own = used && i >= 0 && i < nx;
     const int k0 = seg * A0.seg, k1 = min(k0 + A0.seg, K0.d.n[2]);
     const int ic = min(max(i, 0), nx - 1);   // a cell of the row, also for the lanes at its ends
     const unsigned oc = (unsigned)(ic + nx * j) * 8u;
-    const Source<ROLE == SWEEP_RHS, G> P(K0.d, i, j);
+    const Source<DENSE, G> P(K0.d, i, j);
 
     double q0[9];
 #pragma unroll
@@ -281,6 +296,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             face_solve64<1>(lL, lR, geo_cast<double>(face_geo<1, KIND>(d, x, d.lo[1] + j * d.dx[1], z, f)), d, Fl);
             face_solve64<1>(hL, hR, geo_cast<double>(face_geo<1, KIND>(d, x, d.lo[1] + (j + 1) * d.dx[1], z, f + nx)),
                             d, Fh);
+            if (ROLE == SWEEP_CT && own) {
+                put_transverse<1>(K.A.F[1], d.nf[1], f, Fl);
+                if (j == ny - 1)
+                    put_transverse<1>(K.A.F[1], d.nf[1], f + nx, Fh);
+            }
 #pragma unroll
             for (int v = 0; v < 9; ++v)
                 R[v] = -(Fh[v] - Fl[v]) * d.idx[1];
@@ -315,6 +335,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                 face_solve64<0>(qL, qR, g, d, F);
             else
                 face_solve<0>(qL, qR, g, d, F);   // 1D grids: the plain order of operations
+            if (ROLE == SWEEP_CT && used && i >= 0)
+                put_transverse<0>(K.A.F[0], d.nf[0], f, F);
 #pragma unroll
             for (int v = 0; v < 9; ++v)
                 R[v] -= (from_right(F[v]) - F[v]) * d.idx[0];
@@ -355,6 +377,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                 face_geo<2, KIND>(d, d.lo[0] + (i + 0.5) * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1],
                                   d.lo[2] + (k + 1) * d.dx[2], ic + (long long)nx * (j + (long long)ny * (k + 1))));
             face_solve64<2>(qL, qR, g, d, F);
+            if (ROLE == SWEEP_CT && own) {
+                double Fp[9];
+#pragma unroll
+                for (int v = 5; v < 7; ++v)
+                    Fp[v] = sF[v * 64 + lane];
+                const long long f = ic + (long long)nx * (j + (long long)ny * k);
+                put_transverse<2>(K.A.F[2], d.nf[2], f, Fp);
+                if (k == d.n[2] - 1)
+                    put_transverse<2>(K.A.F[2], d.nf[2], f + (long long)nx * ny, F);
+            }
 #pragma unroll
             for (int v = 0; v < 9; ++v) {
                 R[v] -= (F[v] - sF[v * 64 + lane]) * d.idx[2];
@@ -394,12 +426,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         Geo g;
         add_sources<KIND>(d, d.lo[0] + (i + 0.5) * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1],
                           d.lo[2] + (k + 0.5) * d.dx[2], plane + oc / 8u, q, g, R);
-        if constexpr (ROLE == SWEEP_RHS) {
+        if constexpr (ROLE != SWEEP_STEP) {
             if (own) {
 #pragma unroll
-                for (int v = 0; v < 9; ++v)
+                for (int v = 0; v < (ROLE == SWEEP_CT ? 5 : 9); ++v)
                     buf_store(A.R + v * d.N + plane, oc, R[v]);
-                if (A.Pn)
+                if (ROLE == SWEEP_CT)
+#pragma unroll
+                    for (int a = 0; a < 3; ++a)
+                        if (!d.act[a])
+                            buf_store(A.Ri + plane, oc, R[5 + a]);
+                if (DENSE && A.Pn)
                     sweep_store(A.Pn, d, (unsigned)((j + d.g[1]) * d.px + i + d.g[0]) * 8u, i, j, k, q);
             }
         } else {
@@ -475,7 +512,7 @@ static int sweep_segment(long long ngrp, int nz)
     return best;
 }
 
-template <int ROLE>
+template <int ROLE, bool DENSE>
 static hipError_t launch_sweep_r(int kind, const SweepArgs& A, const Dev& d, hipStream_t s)
 {
     const long long wx = d.act[0] ? d.n[0] + 2 : d.n[0];
@@ -493,11 +530,11 @@ static hipError_t launch_sweep_r(int kind, const SweepArgs& A, const Dev& d, hip
     if (blocks >= (1LL << 31))
         return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks), block(64);
-#define GRMHD_SWEEP(KIND)                                                            \
-    if (d.ppm)                                                                       \
-        hipLaunchKernelGGL((k_sweep<KIND, true, ROLE>), grid, block, 0, s, K);       \
-    else                                                                             \
-        hipLaunchKernelGGL((k_sweep<KIND, false, ROLE>), grid, block, 0, s, K);
+#define GRMHD_SWEEP(KIND)                                                                 \
+    if (d.ppm)                                                                            \
+        hipLaunchKernelGGL((k_sweep<KIND, true, ROLE, DENSE>), grid, block, 0, s, K);     \
+    else                                                                                  \
+        hipLaunchKernelGGL((k_sweep<KIND, false, ROLE, DENSE>), grid, block, 0, s, K);
     if (kind == FLAT) {
         GRMHD_SWEEP(FLAT)
     } else if (kind == ISO) {
@@ -509,9 +546,129 @@ static hipError_t launch_sweep_r(int kind, const SweepArgs& A, const Dev& d, hip
     return hipGetLastError();
 }
 
+// The second half of a flux-CT substep or right-hand side: per cell the field's
+// flux differences from the edge values around it (Toth 2000).  The edge value of
+// the axes (a, b) at a-face fa and b-face fb is
+//   W = 1/4 [F^b(Bd^a) at the two b-faces beside the edge
+//            - F^a(Bd^b) at the two a-faces beside it],
+// the corrected fluxes are F^a(Bd^b) = -1/2 and F^b(Bd^a) = +1/2 the sum of the
+// edge values at a face's two edges.  Every cell forms its four edge values per
+// pair itself, the lower neighbour's term first, so that the cells around an edge
+// agree on its value to the last bit; the caches serve the repeated reads.  The
+// two launches move 560 B a cell; face records, edge values and corrected fluxes
+// as arrays of their own moved 1160 B in six launches.
+template <int KIND, bool RHS>
+__global__ __launch_bounds__(256) void k_ct_update(SweepArgs A, Dev d)
+{
+    const long long c = (long long)blockIdx.x * 256 + threadIdx.x;
+    int nfail = 0, natm = 0, npf = 0, nfb = 0, itmax = 0;
+    if (c < d.N) {
+        int ix[3];
+        if (d.N <= 0x7fffffffLL) {
+            const unsigned cu = (unsigned)c, t = cu / (unsigned)d.n[0];
+            ix[2] = (int)(t / (unsigned)d.n[1]);
+            ix[1] = (int)(t - (unsigned)ix[2] * (unsigned)d.n[1]);
+            ix[0] = (int)(cu - t * (unsigned)d.n[0]);
+        } else {
+            ix[0] = (int)(c % d.n[0]);
+            const long long t = c / d.n[0];
+            ix[1] = (int)(t % d.n[1]);
+            ix[2] = (int)(t / d.n[1]);
+        }
+        double R[9];
+#pragma unroll
+        for (int v = 0; v < 5; ++v)
+            R[v] = A.R5[v * d.N + c];
+#pragma unroll
+        for (int v = 5; v < 9; ++v)
+            R[v] = v < 8 && !d.act[v - 5] ? A.Ri[c] : 0.0;
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            const int a = p == 2 ? 1 : 0, b = p == 0 ? 1 : 2;
+            if (!d.act[a] || !d.act[b])
+                continue;
+            const int ca[3] = {map_cell(ix[a] - 1, d.n[a], d.bc[a]), ix[a], map_cell(ix[a] + 1, d.n[a], d.bc[a])};
+            const int cb[3] = {map_cell(ix[b] - 1, d.n[b], d.bc[b]), ix[b], map_cell(ix[b] + 1, d.n[b], d.bc[b])};
+            auto record = [&](int dir, int v, int ia, int ib) {
+                int q[3] = {ix[0], ix[1], ix[2]};
+                q[a] = ia;
+                q[b] = ib;
+                const long long m0 = d.n[0] + (dir == 0), m1 = d.n[1] + (dir == 1);
+                return A.F[dir][v * d.nf[dir] + (q[2] * m1 + q[1]) * m0 + q[0]];
+            };
+            double gb[3][2], ga[2][3], W[2][2];
+#pragma unroll
+            for (int m = 0; m < 3; ++m)
+#pragma unroll
+                for (int f = 0; f < 2; ++f) {
+                    gb[m][f] = record(b, 5 + a, ca[m], ix[b] + f);
+                    ga[f][m] = record(a, 5 + b, ix[a] + f, cb[m]);
+                }
+#pragma unroll
+            for (int fa = 0; fa < 2; ++fa)
+#pragma unroll
+                for (int fb = 0; fb < 2; ++fb)
+                    W[fa][fb] = 0.25 * ((gb[fa][fb] + gb[fa + 1][fb]) - (ga[fa][fb] + ga[fa][fb + 1]));
+            R[5 + a] -= 0.5 * ((W[0][1] + W[1][1]) - (W[0][0] + W[1][0])) * d.idx[b];
+            R[5 + b] += 0.5 * ((W[1][0] + W[1][1]) - (W[0][0] + W[0][1])) * d.idx[a];
+        }
+        if (RHS) {
+#pragma unroll
+            for (int v = 0; v < 9; ++v)
+                A.R[v * d.N + c] = R[v];
+        } else {
+            const long long pc = cache_index(d, ix[0], ix[1], ix[2]);
+            double q[9], u[9], p[9];
+#pragma unroll
+            for (int v = 0; v < 9; ++v) {
+                q[v] = A.Pc[v * d.sv + pc];
+                const double un = A.Un[v * d.N + c];
+                const double us = A.Us ? A.Us[v * d.N + c] : un;
+                u[v] = us + A.a * (un - us) + A.b * (A.dt * R[v]);
+            }
+            const Geo g = cell_geo<KIND>(d, d.lo[0] + (ix[0] + 0.5) * d.dx[0], d.lo[1] + (ix[1] + 0.5) * d.dx[1],
+                                         d.lo[2] + (ix[2] + 0.5) * d.dx[2], c);
+            int iters = 0;
+            const int flags = recover_cell(d, g, u, q, p, iters);
+#pragma unroll
+            for (int v = 0; v < 9; ++v)
+                A.Uo[v * d.N + c] = u[v];
+            store_prim(d, A.Pn, pc, ix[0], ix[1], ix[2], p);
+            tally(flags, iters, nfail, natm, npf, nfb, itmax);
+        }
+    }
+    if (!RHS)
+        count_sums(A.cnt, nfail, natm, npf, nfb, itmax);
+}
+
+static hipError_t launch_ct_update(int kind, const SweepArgs& A, const Dev& d, hipStream_t s)
+{
+    const dim3 grid((unsigned)((d.N + 255) / 256)), block(256);
+#define GRMHD_CT(KIND)                                                           \
+    if (A.R)                                                                     \
+        hipLaunchKernelGGL((k_ct_update<KIND, true>), grid, block, 0, s, A, d);  \
+    else                                                                         \
+        hipLaunchKernelGGL((k_ct_update<KIND, false>), grid, block, 0, s, A, d);
+    if (kind == FLAT) {
+        GRMHD_CT(FLAT)
+    } else if (kind == ISO) {
+        GRMHD_CT(ISO)
+    } else {
+        GRMHD_CT(STORED)
+    }
+#undef GRMHD_CT
+    return hipGetLastError();
+}
+
 hipError_t launch_sweep(int kind, const SweepArgs& A, const Dev& d, hipStream_t s)
 {
-    return A.R ? launch_sweep_r<SWEEP_RHS>(kind, A, d, s) : launch_sweep_r<SWEEP_STEP>(kind, A, d, s);
+    if (!A.R5)
+        return A.R ? launch_sweep_r<SWEEP_RHS, true>(kind, A, d, s) : launch_sweep_r<SWEEP_STEP, false>(kind, A, d, s);
+    SweepArgs B = A;
+    B.R = A.R5;
+    const hipError_t e =
+        A.R ? launch_sweep_r<SWEEP_CT, true>(kind, B, d, s) : launch_sweep_r<SWEEP_CT, false>(kind, B, d, s);
+    return e == hipSuccess ? launch_ct_update(kind, A, d, s) : e;
 }
 
 }  // namespace grmhd

@@ -35,27 +35,27 @@ def _workload(n, bc, metric, seed):
                        M=1.0 if metric else 0.0)
 
 
-@pytest.mark.parametrize("recon", ["mc", "ppm"])
+@pytest.mark.parametrize("recon,div", [("mc", "cleaning"), ("ppm", "cleaning"), ("mc", "fluxct"), ("ppm", "fluxct")])
 @pytest.mark.parametrize("n", SIZES)
-def test_rhs_and_steps_match_oracle(G, orc, n, recon):
+def test_rhs_and_steps_match_oracle(G, orc, n, recon, div):
     if recon == "ppm" and any(v == 2 for v in n):
         pytest.skip("PPM needs three cells on an active axis")
     for bc, metric in ((WL.PERIODIC, False), (WL.OUTFLOW, True)):
         w = _workload(n, bc, metric, sum(n) + 7 * bc)
-        pb = orc.Problem(recon=int(recon == "ppm"), **w.problem_kwargs())
-        s = G.solver_for(w, device=DEV, reconstruction=recon)
+        pb = orc.Problem(recon=int(recon == "ppm"), ct=int(div == "fluxct"), **w.problem_kwargs())
+        s = G.solver_for(w, device=DEV, reconstruction=recon, divergence=div)
         P = torch.from_numpy(w.P).to(DEV)
         R, Rr = s.rhs(P).cpu().numpy(), orc.rhs(pb, w.P)
         scale = np.abs(Rr).reshape(9, -1).max(axis=1)
         err = np.abs(R - Rr).reshape(9, -1).max(axis=1) / np.maximum(scale, scale.max() * 1e-3)
-        print(w.name, recon, bc, metric, "rhs", err.max(), flush=True)
+        print(w.name, recon, div, bc, metric, "rhs", err.max(), flush=True)
         assert np.all(err <= 1e-11)
         U = s.cons(P)
         for _ in range(w.nsteps):
             s.step(U, w.dt)
         Ur, _, _ = orc.step(pb, orc.prim2con(pb, w.P), w.P, w.dt, w.nsteps)
         err = orc.parity_error(U.cpu().numpy(), Ur)
-        print(w.name, recon, bc, metric, "steps", err.max(), flush=True)
+        print(w.name, recon, div, bc, metric, "steps", err.max(), flush=True)
         assert np.all(err <= 1e-10)
 
 
