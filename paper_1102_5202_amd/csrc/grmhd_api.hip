@@ -490,6 +490,26 @@ int sweep_stage(grmhd_ctx* c, const double* Pc, double* Pn, const double* Un, co
     return timed(c, GRMHD_K_UPDATE, [&] { return grmhd::launch_sweep(c->kind, A, c->d, c->stream); });
 }
 
+// Whether a step stays in registers, stages and all: 1D grids along x, flat
+// metric, MC (a periodic image of a curved metric's face sits elsewhere, and PPM
+// reads a third cell).
+bool in_line(const grmhd_ctx* c)
+{
+    return c->d.act[0] && !c->d.act[1] && !c->d.act[2] && !c->d.ppm && c->kind == grmhd::FLAT;
+}
+
+int line_step(grmhd_ctx* c, double* U, double dt, double* const* stages, unsigned char* fout)
+{
+    const int rc = fluxes<double>(c, 0, 0);   // ghosts only
+    if (rc)
+        return rc;
+    const bool rk3 = c->rk_order == 3;
+    return timed(c, GRMHD_K_UPDATE, [&] {
+        return grmhd::launch_line(c->rk_order, rk3 ? RK3A : RK2A, rk3 ? RK3B : RK2B, cache<double>(c),
+                                  cache<double>(c, 1), U, (double*)c->Us, c->d, dt, c->cnt, stages, fout, c->stream);
+    });
+}
+
 // The update launch of the other substeps, with the stage-state types TS (read)
 // and TO (written).
 template <typename T, typename TS, typename TO>
@@ -519,6 +539,10 @@ int step_t(grmhd_ctx* c, double* U, double dt)
     // type (float in the mixed path); the last stage writes U.
     const bool rotate = sweeps<T>() || fused<T>(c);
     T* Us = (T*)c->Us;
+    if constexpr (sweeps<T>()) {
+        if (in_line(c))
+            return line_step(c, U, dt, nullptr, nullptr);
+    }
     for (int s = 0; s < ns; ++s) {
         const bool first = s == 0, last = s == ns - 1;
         const int src = rotate ? s : 0;
@@ -672,6 +696,13 @@ int step_record(grmhd_ctx* c, double* U, double dt, int slot)
         return GRMHD_ERR_HIP;
     double* Us = (double*)c->Us;
     unsigned char* fl = tape_flags(c, slot);
+    if (in_line(c)) {
+        double* stages[3] = {tape_cache(c, slot, 1), tape_cache(c, slot, 2), ns == 3 ? tape_cache(c, slot, 3) : nullptr};
+        rc = line_step(c, U, dt, stages, fl);
+        if (rc == GRMHD_OK)
+            c->tape_dt[slot] = dt;
+        return rc;
+    }
     for (int s = 0; s < ns; ++s) {
         rc = sweep_stage(c, tape_cache(c, slot, s), tape_cache(c, slot, s + 1), U, s == 0 ? nullptr : Us,
                          s == ns - 1 ? U : Us, dt, A[s], B[s], fl + (size_t)s * c->L.N);

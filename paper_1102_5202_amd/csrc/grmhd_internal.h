@@ -69,6 +69,12 @@ struct SweepArgs {
     int ngrp, nseg, seg;   // set by launch_sweep
 };
 hipError_t launch_sweep(int kind, const SweepArgs& A, const Dev& d, hipStream_t s);
+// One whole FP64 Runge-Kutta step of ns stages (coefficients a, b) on a 1D grid
+// along x (flat metric, MC): U and the cache P0 are advanced in place; U1, P1
+// scratch of their shapes.  stages, fout (null unless recorded): the caches of the
+// stages' primitives and their recovery flags [ns][N].
+hipError_t launch_line(int ns, const double* a, const double* b, double* P0, double* P1, double* U, double* U1, const Dev& d, double dt,
+                       unsigned long long* cnt, double* const* stages, unsigned char* fout, hipStream_t s);
 template <typename T>
 hipError_t launch_rhs(int kind, const T* Fx, const T* Fy, const T* Fz, const T* Pc, double* R,
                       const Dev& d, hipStream_t s);

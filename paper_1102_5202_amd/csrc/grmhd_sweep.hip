@@ -660,6 +660,148 @@ static hipError_t launch_ct_update(int kind, const SweepArgs& A, const Dev& d, h
     return hipGetLastError();
 }
 
+// One whole Runge-Kutta step of a 1D grid along x (flat metric, MC) in a wave's
+// registers: its 64 cells take all stages, and the two cells at either end that
+// each stage's stencil spoils repeat cells of the neighbouring waves (RK3: 52 of 64
+// lanes are its own, RK2: 56).  A periodic image evolves as its cell does; beyond
+// an outflow end the lanes take the end cell's primitives after every stage.
+//   direct: one workgroup of up to 4 waves (one per SIMD) holds the whole grid, so
+//   the new state may be stored in place once all of it has read the old one;
+//   else it goes to Uo and Pn, and k_line_copy takes it over.
+// Bound by the serial chain of the stages (roots, divisions and the Newton
+// iteration of one wave per SIMD).  An RK3 step of 200 cells takes 12.7 us in one
+// launch, of 400 to 2000 cells 14.6 us in two (8 waves in one workgroup: 17.3 us);
+// a launch per stage took 21 us.
+// The stages: Runge-Kutta coefficients, and for a recorded step the caches that
+// keep their primitives (recovery flags in fout).
+struct LineStages {
+    double a[3], b[3];
+    double* P[3];
+};
+
+template <bool RK3>
+__global__ __launch_bounds__(256) void k_line(SweepArgs A, Dev d, LineStages rk, int direct)
+{
+    constexpr int NS = RK3 ? 3 : 2, H = 2 * NS, OWN = 64 - 2 * H;
+    const int lane = threadIdx.x & 63, n = d.n[0];
+    const int wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    const int c0 = wave * OWN - H, c = c0 + lane;
+    int im = c;
+    if (d.bc[0] == 0) {
+        im = c % n;
+        im += im < 0 ? n : 0;
+    } else {
+        im = min(max(c, 0), n - 1);
+    }
+    const bool own = lane >= H && lane < 64 - H && c < n;
+    double q[9], un[9], ub[9];
+#pragma unroll
+    for (int v = 0; v < 9; ++v) {
+        q[v] = A.Pc[v * d.sv + d.g[0] + im];
+        un[v] = A.Un[v * d.N + im];
+        ub[v] = un[v];
+    }
+    if (direct)
+        __syncthreads();
+    int nfail = 0, natm = 0, npf = 0, nfb = 0, itmax = 0;
+    const Geo g = geo_at<FLAT>(d, 0.0, 0.0, 0.0);
+#pragma nounroll
+    for (int s = 0; s < NS; ++s) {
+        const double a = rk.a[s], b = rk.b[s];
+        double qL[9], qR[9], F[9], R[9];
+#pragma unroll
+        for (int v = 0; v < 9; ++v) {
+            const double h = mc_hslope(from_left(q[v]), q[v], from_right(q[v]));
+            qR[v] = q[v] - h;
+            qL[v] = from_left(q[v] + h);
+        }
+        face_solve<0>(qL, qR, geo_cast<double>(g), d, F);
+#pragma unroll
+        for (int v = 0; v < 9; ++v)
+            R[v] = -(from_right(F[v]) - F[v]) * d.idx[0];
+        Geo gs;
+        add_sources<FLAT>(d, 0.0, 0.0, 0.0, 0, q, gs, R);
+        double u[9], p[9];
+#pragma unroll
+        for (int v = 0; v < 9; ++v)
+            u[v] = ub[v] + a * (un[v] - ub[v]) + b * (A.dt * R[v]);
+        // lanes whose stencil is still whole (the others' values are not used)
+        if (lane >= 2 * (s + 1) && lane < 64 - 2 * (s + 1) && (d.bc[0] == 0 || (c >= 0 && c < n))) {
+            int iters = 0;
+            const int flags = recover_cell(d, g, u, q, p, iters);
+#pragma unroll
+            for (int v = 0; v < 9; ++v) {
+                q[v] = p[v];
+                ub[v] = u[v];
+            }
+            if (own) {
+                tally(flags, iters, nfail, natm, npf, nfb, itmax);
+                if (rk.P[s]) {
+                    store_prim(d, rk.P[s], cache_index(d, c, 0, 0), c, 0, 0, q);
+                    A.fout[s * d.N + c] = (unsigned char)flags;
+                }
+            }
+        }
+        if (d.bc[0] != 0) {
+            const int end = c < 0 ? -c0 : min(n - 1 - c0, 63);   // the lane of the end cell
+#pragma unroll
+            for (int v = 0; v < 9; ++v) {
+                const double e = __shfl(q[v], end);
+                q[v] = c < 0 || c >= n ? e : q[v];
+            }
+        }
+    }
+    if (own) {
+#pragma unroll
+        for (int v = 0; v < 9; ++v)
+            A.Uo[v * d.N + c] = ub[v];
+        store_prim(d, A.Pn, cache_index(d, c, 0, 0), c, 0, 0, q);
+    }
+    count_sums(A.cnt, nfail, natm, npf, nfb, itmax);
+}
+
+// The state k_line left beside the caller's (U, and the primitive rows) into it.
+__global__ __launch_bounds__(256) void k_line_copy(const double* __restrict__ Us, double* __restrict__ U, long long nu,
+                                                   const double* __restrict__ Ps, double* __restrict__ P, long long np)
+{
+    const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (t < nu)
+        U[t] = Us[t];
+    if (t < np)
+        P[t] = Ps[t];
+}
+
+hipError_t launch_line(int ns, const double* a, const double* b, double* P0, double* P1, double* U, double* U1, const Dev& d, double dt,
+                       unsigned long long* cnt, double* const* stages, unsigned char* fout, hipStream_t s)
+{
+    const int own = 64 - 4 * ns, waves = (d.n[0] + own - 1) / own;
+    const bool direct = waves <= 4;
+    SweepArgs A{};
+    A.Pc = P0;
+    A.Pn = direct ? P0 : P1;
+    A.Un = U;
+    A.Uo = direct ? U : U1;
+    A.cnt = cnt;
+    A.fout = fout;
+    A.dt = dt;
+    LineStages rk{};
+    for (int k = 0; k < ns; ++k) {
+        rk.a[k] = a[k];
+        rk.b[k] = b[k];
+        rk.P[k] = stages ? stages[k] : nullptr;
+    }
+    const dim3 grid(direct ? 1 : waves), block(direct ? 64 * waves : 64);
+    if (ns == 3)
+        hipLaunchKernelGGL((k_line<true>), grid, block, 0, s, A, d, rk, (int)direct);
+    else
+        hipLaunchKernelGGL((k_line<false>), grid, block, 0, s, A, d, rk, (int)direct);
+    if (!direct) {
+        const long long nu = 9 * d.N, np = 9 * d.sv;
+        hipLaunchKernelGGL(k_line_copy, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, s, U1, U, nu, P1, P0, np);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_sweep(int kind, const SweepArgs& A, const Dev& d, hipStream_t s)
 {
     if (!A.R5)

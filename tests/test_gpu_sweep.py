@@ -71,3 +71,26 @@ def test_rhs_loads_the_cache(G):
     a.step(Ua, w.dt)
     b.step(Ub, w.dt)
     assert torch.equal(Ua, Ub)
+
+
+@pytest.mark.parametrize("rk", [2, 3])
+@pytest.mark.parametrize("bc", [WL.PERIODIC, WL.OUTFLOW])
+@pytest.mark.parametrize("n", [2, 3, 5, 52, 53, 56, 57, 208, 209, 224, 225, 700])
+def test_line_step(G, orc, n, bc, rk):
+    """A whole step of a 1D grid in registers, at the edges of a wave's own cells
+    (52 with RK3, 56 with RK2) and of one workgroup's (4 waves): bitwise as
+    recorded, and the oracle's within its bar."""
+    w = _workload((n, 1, 1), bc, False, n + rk)
+    w.rk_order = rk
+    P = torch.from_numpy(w.P).to(DEV)
+    a, b = G.solver_for(w, device=DEV), G.solver_for(w, device=DEV, adjoint=True, tape_steps=1)
+    Ua, Ub = a.cons(P), b.cons(P)
+    for _ in range(3):
+        a.step(Ua, w.dt)
+        b.step_record(Ub, w.dt, 0)
+        assert torch.equal(Ua, Ub)
+    assert torch.equal(a.prim(Ua), b.prim(Ub))
+    assert a.status() == b.status()
+    pb = orc.Problem(**w.problem_kwargs())
+    Ur, _, _ = orc.step(pb, orc.prim2con(pb, w.P), w.P, w.dt, 3)
+    assert np.all(orc.parity_error(Ua.cpu().numpy(), Ur) <= 1e-10)
