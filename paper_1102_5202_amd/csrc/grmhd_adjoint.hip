@@ -64,7 +64,7 @@ __device__ __forceinline__ void face_flux_rev(const double* qL0, const double* q
                                               double z, const Dev& d, const double* Fb, double* qLb,
                                               double* qRb)
 {
-    const GeoT<double> g = geo_cast<double>(geo_at<KIND>(d, x, y, z));
+    const GeoT<double> g = geo_cast<double>(geo_at<KIND, double>(d, x, y, z));
     double qL[9], qR[9];
 #pragma unroll
     for (int v = 0; v < 9; ++v) {
@@ -317,7 +317,7 @@ __device__ __forceinline__ void sources_rev(const Dev& d, double x, double y, do
     if (KIND == FLAT)
         return;
     double ka, kp;
-    const Geo g0 = geo_deriv<KIND>(d, x, y, z, ka, kp);
+    const Geo g0 = geo_deriv<KIND, double>(d, x, y, z, ka, kp);
     const GeoT<double> g = geo_cast<double>(g0);
     const Kin<double> k = kinematics(q, g, d.gfac);
     const double ia2 = 1.0 / (g.alpha * g.alpha);
@@ -349,7 +349,7 @@ __device__ __forceinline__ bool recovery_adjoint(const Dev& d, const double3& x,
                                                  const double* y, double* out, double J[5][8],
                                                  GeoT<double>& g)
 {
-    g = geo_cast<double>(geo_at<KIND>(d, x.x, x.y, x.z));
+    g = geo_cast<double>(geo_at<KIND, double>(d, x.x, x.y, x.z));
     cons_jacobian(q, g, d.gfac, J);
     return cons_jacobian_solve_t(J, g.sqrtmg, y, out);
 }
@@ -366,7 +366,7 @@ __device__ __forceinline__ void rec_adjoint(const Dev& d, const double3& x, cons
     if (fl & FLAG_ATM) {
         // hydro primitives constant; B = Bd / sqrt(-g), Phi passed through;
         // the matter part of U rebuilt from (constant hydro, B)
-        g = geo_cast<double>(geo_at<KIND>(d, x.x, x.y, x.z));
+        g = geo_cast<double>(geo_at<KIND, double>(d, x.x, x.y, x.z));
         cons_jacobian(q, g, d.gfac, J);
 #pragma unroll
         for (int e = 5; e < 8; ++e) {
@@ -382,7 +382,7 @@ __device__ __forceinline__ void rec_adjoint(const Dev& d, const double3& x, cons
         ut[8] = ub[8] + pb[8];
     } else if (fl & FLAG_FAIL) {
         // the previous hydro primitives are kept: no derivative through them
-        g = geo_cast<double>(geo_at<KIND>(d, x.x, x.y, x.z));
+        g = geo_cast<double>(geo_at<KIND, double>(d, x.x, x.y, x.z));
 #pragma unroll
         for (int r = 0; r < 5; ++r)
             ut[r] = ub[r];
@@ -392,7 +392,7 @@ __device__ __forceinline__ void rec_adjoint(const Dev& d, const double3& x, cons
         ut[8] = ub[8] + pb[8];
     } else if (fl & FLAG_PFLOOR) {
         // pressure constant; rho, u~ from the root; matter part rebuilt
-        g = geo_cast<double>(geo_at<KIND>(d, x.x, x.y, x.z));
+        g = geo_cast<double>(geo_at<KIND, double>(d, x.x, x.y, x.z));
         cons_jacobian(q, g, d.gfac, J);
         double pt[9];
 #pragma unroll
@@ -698,7 +698,7 @@ __global__ __launch_bounds__(ABLOCK) void k_adj_cons(const double* __restrict__ 
         ub[v] = Ubar[v * d.N + c];
     }
     const double3 x = centre(d, i, j, k);
-    const GeoT<double> g = geo_cast<double>(geo_at<KIND>(d, x.x, x.y, x.z));
+    const GeoT<double> g = geo_cast<double>(geo_at<KIND, double>(d, x.x, x.y, x.z));
     double J[5][8];
     cons_jacobian(q, g, d.gfac, J);
 #pragma unroll

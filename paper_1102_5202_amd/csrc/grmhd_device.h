@@ -67,6 +67,22 @@ __device__ __forceinline__ double fast_rcp(double x)
     return fma(r, fma(e, e, e), r);
 }
 
+// The reciprocal (square root) in the FP64 parts of a path with primitives of
+// type T: FP64 takes the forms above, mixed precision the library ones, whose
+// bits its stated results carry (a last-bit change there moves the rounding to
+// FP32 now and then, by 6e-8 of a value).
+template <typename T>
+__device__ __forceinline__ double rsqrt_of(double x)
+{
+    return sizeof(T) == sizeof(double) ? fast_rsqrt(x) : rsqrt(x);
+}
+
+template <typename T>
+__device__ __forceinline__ double rcp_of(double x)
+{
+    return sizeof(T) == sizeof(double) ? fast_rcp(x) : 1.0 / x;
+}
+
 // Geometry at one point.
 struct Geo {
     double alpha, psi4, ipsi4, sqrtg, sqrtmg, isqrtmg;
@@ -74,22 +90,24 @@ struct Geo {
 
 // 1/r_s at a point (r_s the softened radius); varying is false where r_s is
 // constant (MAX softening inside r_min: derivatives vanish).
+template <typename T>
 __device__ __forceinline__ double soft_iradius(const Dev& d, double r2, bool& varying)
 {
     if (d.soft == 0) {
         varying = true;
-        return fast_rsqrt(r2 + d.rmin2);
+        return rsqrt_of<T>(r2 + d.rmin2);
     }
     varying = r2 > d.rmin2;
-    return fast_rsqrt(varying ? r2 : d.rmin2);
+    return rsqrt_of<T>(varying ? r2 : d.rmin2);
 }
 
 // The isotropic metric from h = M / (2 r_s) < 1: alpha = (1-h)/(1+h),
 // psi = 1 + h, with one division for 1/(1+h) and 1/(1-h).
+template <typename T>
 __device__ __forceinline__ Geo geo_from_h(double h, double& i1h)
 {
     Geo g;
-    const double q = fast_rcp((1.0 - h) * (1.0 + h));
+    const double q = rcp_of<T>((1.0 - h) * (1.0 + h));
     i1h = (1.0 - h) * q;                  // 1 / (1 + h)
     const double im1h = (1.0 + h) * q;    // 1 / (1 - h)
     const double psi = 1.0 + h;
@@ -117,7 +135,7 @@ __device__ __forceinline__ Geo geo_from_ap(double alpha, double psi4)
     return g;
 }
 
-template <int KIND>
+template <int KIND, typename T>
 __device__ __forceinline__ Geo geo_at(const Dev& d, double x, double y, double z)
 {
     if (KIND == FLAT) {
@@ -126,14 +144,14 @@ __device__ __forceinline__ Geo geo_at(const Dev& d, double x, double y, double z
         return g;
     }
     bool vary;
-    const double irs = soft_iradius(d, x * x + y * y + z * z, vary);
+    const double irs = soft_iradius<T>(d, x * x + y * y + z * z, vary);
     double i1h;
-    return geo_from_h(0.5 * d.M * irs, i1h);
+    return geo_from_h<T>(0.5 * d.M * irs, i1h);
 }
 
 // Geometry plus the radial derivative factors at a cell centre:
 // d_j alpha = ka * x_j and d_j psi^4 = kp * x_j.
-template <int KIND>
+template <int KIND, typename T>
 __device__ __forceinline__ Geo geo_deriv(const Dev& d, double x, double y, double z, double& ka,
                                          double& kp)
 {
@@ -144,10 +162,10 @@ __device__ __forceinline__ Geo geo_deriv(const Dev& d, double x, double y, doubl
         return g;
     }
     bool vary;
-    const double irs = soft_iradius(d, x * x + y * y + z * z, vary);
+    const double irs = soft_iradius<T>(d, x * x + y * y + z * z, vary);
     const double h = 0.5 * d.M * irs;
     double i1h;
-    const Geo g = geo_from_h(h, i1h);
+    const Geo g = geo_from_h<T>(h, i1h);
     const double psi = 1.0 + h;
     const double hr2 = vary ? h * irs * irs : 0.0;
     // d alpha/d r_s = 2 h / (r_s (1+h)^2), d psi^4/d r_s = -4 psi^3 h / r_s, d r_s/d x_j = x_j / r_s
@@ -158,20 +176,20 @@ __device__ __forceinline__ Geo geo_deriv(const Dev& d, double x, double y, doubl
 
 // Geometry at face f of axis D (position x, y, z) and at the centre of cell c
 // (position x, y, z): closed form, or the stored values.
-template <int D, int KIND>
+template <int D, int KIND, typename T>
 __device__ __forceinline__ Geo face_geo(const Dev& d, double x, double y, double z, long long f)
 {
     if (KIND == STORED)
         return geo_from_ap(d.mf[D][f], d.mf[D][d.nf[D] + f]);
-    return geo_at<KIND>(d, x, y, z);
+    return geo_at<KIND, T>(d, x, y, z);
 }
 
-template <int KIND>
+template <int KIND, typename T>
 __device__ __forceinline__ Geo cell_geo(const Dev& d, double x, double y, double z, long long c)
 {
     if (KIND == STORED)
         return geo_from_ap(d.mc[c], d.mc[d.N + c]);
-    return geo_at<KIND>(d, x, y, z);
+    return geo_at<KIND, T>(d, x, y, z);
 }
 
 // The face physics below is written for a scalar type T: double for the FP64
@@ -510,7 +528,7 @@ template <int D, int KIND, typename T>
 __device__ __forceinline__ void face_flux(T* qL, T* qR, double x, double y, double z, long long f,
                                           const Dev& d, T* Fo)
 {
-    face_solve_t<D>(qL, qR, geo_cast<T>(face_geo<D, KIND>(d, x, y, z, f)), d, Fo);
+    face_solve_t<D>(qL, qR, geo_cast<T>(face_geo<D, KIND, T>(d, x, y, z, f)), d, Fo);
 }
 
 
@@ -544,7 +562,7 @@ __device__ __forceinline__ void add_sources(const Dev& d, double x, double y, do
         return;
     }
     double ka, kp;
-    g = geo_deriv<KIND>(d, x, y, z, ka, kp);
+    g = geo_deriv<KIND, T>(d, x, y, z, ka, kp);
     if (KIND != FLAT) {
         const GeoT<T> gt = geo_cast<T>(g);
         Kin<T> kk = kinematics(q, gt, (T)d.gfac);
@@ -576,6 +594,7 @@ struct C2P {
 // guess in its last bits); the final point must then satisfy both equations
 // to 1e-10 of their scales with v^2 inside (0, 1) unclamped.  Returns true
 // on acceptance; iters counts the iterations.
+template <typename T>
 __device__ __forceinline__ bool c2p_newton2d(const C2P& c, double gk, double tol, int maxit,
                                              double& Wc, double& v2, int& iters)
 {
@@ -585,9 +604,9 @@ __device__ __forceinline__ bool c2p_newton2d(const C2P& c, double gk, double tol
     for (int it = 0; it < maxit; ++it) {
         iters = it + 1;
         double bw = c.Bc2 + Wc;
-        double iW = fast_rcp(Wc);
+        double iW = rcp_of<T>(Wc);
         double iW2 = iW * iW;
-        double is = fast_rsqrt(1.0 - v2);     // 1 / sqrt(1 - v^2) = W
+        double is = rsqrt_of<T>(1.0 - v2);   // 1 / sqrt(1 - v^2) = W
         double s = (1.0 - v2) * is;
         // residuals
         double r1 = v2 * bw * bw - c.QB2 * (c.Bc2 + 2.0 * Wc) * iW2 - c.Qt2;
@@ -598,7 +617,7 @@ __device__ __forceinline__ bool c2p_newton2d(const C2P& c, double gk, double tol
         double a12 = bw * bw;
         double a21 = -c.QB2 * iW2 * iW - 1.0 + gk * (1.0 - v2);
         double a22 = -0.5 * c.Bc2 + gk * (-Wc + 0.5 * c.D * is);
-        double idet = fast_rcp(a11 * a22 - a12 * a21);
+        double idet = rcp_of<T>(a11 * a22 - a12 * a21);
         double dW = (r1 * a22 - a12 * r2) * idet;
         double dv = (a11 * r2 - a21 * r1) * idet;
         double Wn = Wc - dW;
@@ -807,6 +826,7 @@ enum { FLAG_FAIL = 1, FLAG_ATM = 2, FLAG_PFLOOR = 4, FLAG_FALLBACK = 8 };
 // Recovery plus the atmosphere/floor policy for one cell.  u is the conserved
 // state (its matter part is rewritten where a floor fired), qg the guess (the
 // previous primitives of the cell), p the output primitives.  Returns flags.
+template <typename T>
 __device__ __forceinline__ int recover_cell(const Dev& d, const Geo& g, double* u, const double* qg,
                                             double* p, int& iters)
 {
@@ -841,7 +861,7 @@ __device__ __forceinline__ int recover_cell(const Dev& d, const Geo& g, double* 
         v2 = uu / Wg2;
         bool guess_ok = finite(Wc) && Wc > 0.0 && finite(v2);
         bool conv = guess_ok && (d.c2p1d ? c2p_newton1d(c, d.gk, d.tol, d.maxit, Wc, v2, iters)
-                                         : c2p_newton2d(c, d.gk, d.tol, d.maxit, Wc, v2, iters));
+                                         : c2p_newton2d<T>(c, d.gk, d.tol, d.maxit, Wc, v2, iters));
         if (!conv) {
             flags |= FLAG_FALLBACK;
             WV r = c2p_bracketed(c.D, c.Qn, c.Qt2, c.Bc2, c.QB2, d.gk);
@@ -851,7 +871,7 @@ __device__ __forceinline__ int recover_cell(const Dev& d, const Geo& g, double* 
         }
     }
     if (ok) {
-        double W = fast_rsqrt(1.0 - v2);
+        double W = rsqrt_of<T>(1.0 - v2);
         double s = (1.0 - v2) * W;
         p[0] = c.D * s;
         p[1] = d.gk * (Wc * (1.0 - v2) - c.D * s);

@@ -425,7 +425,7 @@ __device__ __forceinline__ int stage_finish(const Dev& d, const Geo& g, const do
         u[v] = us[v] + a * (un[v] - us[v]) + b * (dt * R[v]);
         qg[v] = (double)q[v];
     }
-    int flags = recover_cell(d, g, u, qg, p, iters);
+    int flags = recover_cell<T>(d, g, u, qg, p, iters);
 #pragma unroll
     for (int v = 0; v < 9; ++v) {
         if constexpr (NT)
@@ -548,7 +548,7 @@ __device__ __forceinline__ void tile_face(const T* sP, int dir, int base, int st
         const long long nf = dir == 0 ? d.nf[0] : d.nf[1];
         g = geo_from_ap(mf[fglob], mf[nf + fglob]);
     } else {
-        g = geo_at<KIND>(d, fx, fy, fz);
+        g = geo_at<KIND, T>(d, fx, fy, fz);
     }
     face_solve_t<0>(qL, qR, geo_cast<T>(g), d, Fo);
 #pragma unroll
@@ -556,30 +556,12 @@ __device__ __forceinline__ void tile_face(const T* sP, int dir, int base, int st
         sF[vo[v] * nslot + slot] = Fo[v];
 }
 
-template <typename T, typename TS, typename TO>
-struct SubstepArgs {
-    const T* Pc;
-    T* Pn;
-    const double* Un;
-    const TS* Us;
-    TO* Uout;
-    double dt, a, b;
-    unsigned long long* cnt;
-    unsigned char* fout;
-    int ntx, ntiles;
-    Dev d;
-};
-
 template <int KIND, int TX, int TY, int SEG, bool NT, typename T, typename TS, typename TO>
 __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_substep(
-    SubstepArgs<T, TS, TO>)
+    const T* __restrict__ Pc, T* __restrict__ Pn, const double* Un, const TS* Us, TO* Uout, Dev d, double dt,
+    double a, double b, unsigned long long* __restrict__ cnt, unsigned char* __restrict__ fout, int ntx, int ntiles)
 {
     using G = Tile<TX, TY>;
-    using Args = SubstepArgs<T, TS, TO>;
-    const Args K0 = kernel_args<Args>();
-    const Dev& d = K0.d;
-    const T* Pc = K0.Pc;
-    const int ntx = K0.ntx, ntiles = K0.ntiles;
     // The staged planes and the face fluxes are double buffered (70.8 KB of
     // LDS, two workgroups per CU): the faces of plane k + 1 and the update of
     // plane k share one barrier interval.
@@ -673,10 +655,9 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2)))
     T hv[9];
     auto halo_load = [&](int k) {
         if (hslot >= 0) {
-            const Args K = kernel_args<Args>();
 #pragma unroll
             for (int v = 0; v < 9; ++v)
-                hv[v] = K.Pc[v * K.d.sv + hoff + (long long)k * st];
+                hv[v] = Pc[v * d.sv + hoff + (long long)k * st];
         }
     };
     auto stage = [&](int k, int pb, const T* own, bool hv_loaded) {
@@ -686,11 +667,10 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2)))
             for (int v = 0; v < 9; ++v)
                 P[v * G::PLANE + oslot] = own[v];
         } else if (own_ghost) {
-            const Args K = kernel_args<Args>();
             const long long o = col + (long long)k * st;
 #pragma unroll
             for (int v = 0; v < 9; ++v)
-                P[v * G::PLANE + oslot] = K.Pc[v * K.d.sv + o];
+                P[v * G::PLANE + oslot] = Pc[v * d.sv + o];
         }
         if (hslot >= 0) {
             if (!hv_loaded)
@@ -707,8 +687,6 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2)))
     // row and column.  One face solver serves both axes (a loop, not
     // unrolled, keeps one copy of its code).
     auto faces = [&](int k, int pb, int fb) {
-        const Args K = kernel_args<Args>();
-        const Dev& d = K.d;
         const double zc = d.lo[2] + (k + 0.5) * d.dx[2];
         const int ntask = t >= G::NT - 64 ? 3 : 2;
 #pragma nounroll
@@ -746,15 +724,13 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2)))
                 halo_load(kh);
             return;
         }
-        const Args K = kernel_args<Args>();
-        const Dev& d = K.d;
         const long long c = i + (long long)nx * (j + (long long)ny * k);
         double un[9], us[9];
-        stage_load<NT>(d, K.Un, K.Us, c, un, us);
+        stage_load<NT>(d, Un, Us, c, un, us);
         T qd[9];
 #pragma unroll
         for (int v = 0; v < 9; ++v)
-            qd[v] = K.Pc[v * d.sv + col + (long long)(k + 2) * st];
+            qd[v] = Pc[v * d.sv + col + (long long)(k + 2) * st];
         T q[9], qL[9], qR[9], Fc[9];
 #pragma unroll
         for (int v = 0; v < 9; ++v) {
@@ -791,9 +767,8 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2)))
         if (kh >= 0)
             halo_load(kh);
         int iters = 0;
-        const Args L = kernel_args<Args>();
-        int flags = stage_finish<NT>(L.d, g, R, q, un, us, L.Uout, c, L.Pn, col + (long long)k * st, i, j, k, L.dt, L.a,
-                                     L.b, L.fout, iters);
+        int flags = stage_finish<NT>(d, g, R, q, un, us, Uout, c, Pn, col + (long long)k * st, i, j, k, dt, a, b,
+                                     fout, iters);
         tally(flags, iters, nfail, natm, npf, nfb, itmax);
     };
 
@@ -804,9 +779,9 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if (k0 + 1 < k1)
         stage(k0 + 1, 1, qc, false);
     __syncthreads();
-    // plane k: the faces of k + 1, the update of k, the staging of k + 2 (into
-    // the buffer plane k used; its own cell is the window's qc once the update
-    // has moved the window up)
+    // plane k: the faces of k + 1, the update of k, the staging of k + 2
+    // (into the buffer plane k used; its own cell is the window's qc once
+    // the update has moved the window up)
     for (int k = k0; k < k1; ++k) {
         const int cur = (k - k0) & 1, nxt = cur ^ 1;
         if (k + 1 < k1)
@@ -816,7 +791,7 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2)))
             stage(k + 2, cur, qc, true);
         __syncthreads();
     }
-    count_sums(kernel_args<Args>().cnt, nfail, natm, npf, nfb, itmax);
+    count_sums(cnt, nfail, natm, npf, nfb, itmax);
 }
 
 template <int KIND, typename T>
@@ -863,7 +838,7 @@ __global__ __launch_bounds__(BLOCK) void k_cons(const double* __restrict__ P, do
         q[v] = P[v * d.N + c];
     store_prim(d, Pc, pc, i, j, k, q);
     if (U) {
-        const GeoT<double> g = geo_cast<double>(cell_geo<KIND>(
+        const GeoT<double> g = geo_cast<double>(cell_geo<KIND, T>(
             d, d.lo[0] + (i + 0.5) * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1], d.lo[2] + (k + 0.5) * d.dx[2], c));
         Kin<double> kk = kinematics(q, g, d.gfac);
 #pragma unroll
@@ -893,10 +868,10 @@ __global__ __launch_bounds__(BLOCK) void k_prim(const double* __restrict__ U, do
             q[v] = (double)Pc[v * d.sv + pc];
             u[v] = U[v * d.N + c];
         }
-        Geo g = cell_geo<KIND>(d, d.lo[0] + (i + 0.5) * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1],
+        Geo g = cell_geo<KIND, T>(d, d.lo[0] + (i + 0.5) * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1],
                                d.lo[2] + (k + 0.5) * d.dx[2], c);
         int iters = 0;
-        int flags = recover_cell(d, g, u, q, p, iters);
+        int flags = recover_cell<T>(d, g, u, q, p, iters);
 #pragma unroll
         for (int v = 0; v < 9; ++v)
             P[v * d.N + c] = p[v];
@@ -981,7 +956,7 @@ __global__ __launch_bounds__(BLOCK) void k_batch_cons(const BatchProb* __restric
         q[v] = P[9 * pr.off + (long long)v * pr.n + c];
     row_store(Prow + pr.poff, pr.n + 4, pr.n, d.bc[0], c, q);
     if (U) {
-        const GeoT<double> gt = geo_cast<double>(geo_at<FLAT>(d, 0.0, 0.0, 0.0));
+        const GeoT<double> gt = geo_cast<double>(geo_at<FLAT, T>(d, 0.0, 0.0, 0.0));
         const Kin<double> kk = kinematics(q, gt, d.gfac);
 #pragma unroll
         for (int v = 0; v < 8; ++v)
@@ -1009,9 +984,9 @@ __global__ __launch_bounds__(BLOCK) void k_batch_prim(const BatchProb* __restric
             u[v] = U[9 * pr.off + (long long)v * pr.n + c];
             q[v] = (double)Prow[pr.poff + v * pitch + c + 2];
         }
-        const Geo geo = geo_at<FLAT>(d, 0.0, 0.0, 0.0);
+        const Geo geo = geo_at<FLAT, T>(d, 0.0, 0.0, 0.0);
         int iters = 0;
-        const int flags = recover_cell(d, geo, u, q, p, iters);
+        const int flags = recover_cell<T>(d, geo, u, q, p, iters);
 #pragma unroll
         for (int v = 0; v < 9; ++v)
             P[9 * pr.off + (long long)v * pr.n + c] = p[v];
@@ -1059,7 +1034,7 @@ __global__ __launch_bounds__(NT) void k_batch_evolve(BatchProb* __restrict__ pro
     const int c0 = min((int)threadIdx.x * ch, n), c1 = min(c0 + ch, n);
     double* Ub = U + 9 * pr.off;
     T* Usb = Us + 9 * pr.off;
-    const Geo geo = geo_at<FLAT>(d, 0.0, 0.0, 0.0);
+    const Geo geo = geo_at<FLAT, T>(d, 0.0, 0.0, 0.0);
     int nfail = 0, natm = 0, npf = 0, nfb = 0, itmax = 0;
     for (int step = 0; step < nsteps; ++step) {
         for (int s = 0; s < ns; ++s) {
@@ -1105,7 +1080,7 @@ __global__ __launch_bounds__(NT) void k_batch_evolve(BatchProb* __restrict__ pro
                     qg[v] = (double)q[v];
                 }
                 int iters = 0;
-                const int flags = recover_cell(d, geo, u, qg, p, iters);
+                const int flags = recover_cell<T>(d, geo, u, qg, p, iters);
                 tally(flags, iters, nfail, natm, npf, nfb, itmax);
                 if (s == ns - 1) {
 #pragma unroll
@@ -1291,7 +1266,7 @@ void k_batch_split(
         T* Usb = Us + 9 * pr.off;
         T* cur = Prow + pr.poff;
         T* nxt = Pnext + pr.poff;
-        const Geo geo = geo_at<FLAT>(d, 0.0, 0.0, 0.0);
+        const Geo geo = geo_at<FLAT, T>(d, 0.0, 0.0, 0.0);
         for (int i = 0; i < nsub && !stalled; ++i) {
             if (i > 0 && !split_wait(flags, pt.left, pt.right, base + i, &s_ok)) {
                 stalled = true;
@@ -1343,7 +1318,7 @@ void k_batch_split(
                         qg[v] = (double)q[v];
                     }
                     int iters = 0;
-                    const int fl = recover_cell(d, geo, u, qg, p, iters);
+                    const int fl = recover_cell<T>(d, geo, u, qg, p, iters);
                     tally(fl, iters, nfail, natm, npf, nfb, itmax);
                     if (s == ns - 1) {
     #pragma unroll
@@ -1637,13 +1612,15 @@ static void launch_substep_nt(int kind, const T* Pc, T* Pn, const double* Un, co
     const int ntiles = ntx * nty;
     const long long nseg = (d.n[2] + SEG - 1) / SEG;
     const dim3 grid((unsigned)(ntiles * nseg)), block(TX * TY);
-    const SubstepArgs<T, TS, TO> A{Pc, Pn, Un, Us, Uout, dt, a, b, cnt, fout, ntx, ntiles, d};
     if (kind == FLAT)
-        hipLaunchKernelGGL((k_substep<FLAT, TX, TY, SEG, NT, T, TS, TO>), grid, block, 0, s, A);
+        hipLaunchKernelGGL((k_substep<FLAT, TX, TY, SEG, NT, T, TS, TO>), grid, block, 0, s, Pc, Pn, Un, Us, Uout, d,
+                           dt, a, b, cnt, fout, ntx, ntiles);
     else if (kind == ISO)
-        hipLaunchKernelGGL((k_substep<ISO, TX, TY, SEG, NT, T, TS, TO>), grid, block, 0, s, A);
+        hipLaunchKernelGGL((k_substep<ISO, TX, TY, SEG, NT, T, TS, TO>), grid, block, 0, s, Pc, Pn, Un, Us, Uout, d,
+                           dt, a, b, cnt, fout, ntx, ntiles);
     else
-        hipLaunchKernelGGL((k_substep<STORED, TX, TY, SEG, NT, T, TS, TO>), grid, block, 0, s, A);
+        hipLaunchKernelGGL((k_substep<STORED, TX, TY, SEG, NT, T, TS, TO>), grid, block, 0, s, Pc, Pn, Un, Us, Uout,
+                           d, dt, a, b, cnt, fout, ntx, ntiles);
 }
 
 template <typename T, typename TS, typename TO>
@@ -1651,7 +1628,9 @@ hipError_t launch_substep(int kind, const T* Pc, T* Pn, const double* Un, const 
                           double dt, double a, double b, unsigned long long* cnt, unsigned char* fout, hipStream_t s)
 {
     // planes per workgroup: the long segment where it still gives enough
-    // workgroups to fill the GPU, else a short one (small grids)
+    // workgroups to fill the GPU, else a short one (small grids); where segments
+    // meet decides between two equal orders of an FP32 face, so the lengths also
+    // belong to the path's results
     const long long tiles = (long long)((d.n[0] + SUB_TX - 1) / SUB_TX) * ((d.n[1] + SUB_TY - 1) / SUB_TY);
     const bool lng = tiles * ((d.n[2] + SUB_SEG - 1) / SUB_SEG) >= SUB_MIN_BLOCKS;
     if (d.nt && lng)

@@ -251,7 +251,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             if (PPM)
                 sM[v * 64 + lane] = q[-1 + G];
         }
-        const Geo g = face_geo<2, KIND>(d, d.lo[0] + (i + 0.5) * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1],
+        const Geo g = face_geo<2, KIND, double>(d, d.lo[0] + (i + 0.5) * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1],
                                         d.lo[2] + k0 * d.dx[2], ic + (long long)nx * (j + (long long)ny * k0));
         face_solve64<2>(qL, qR, geo_cast<double>(g), d, F);
 #pragma unroll
@@ -293,8 +293,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             }
             const double x = d.lo[0] + (i + 0.5) * d.dx[0], z = d.lo[2] + (k + 0.5) * d.dx[2];
             const long long f = ic + (long long)nx * (j + (long long)(ny + 1) * k);
-            face_solve64<1>(lL, lR, geo_cast<double>(face_geo<1, KIND>(d, x, d.lo[1] + j * d.dx[1], z, f)), d, Fl);
-            face_solve64<1>(hL, hR, geo_cast<double>(face_geo<1, KIND>(d, x, d.lo[1] + (j + 1) * d.dx[1], z, f + nx)),
+            face_solve64<1>(lL, lR, geo_cast<double>(face_geo<1, KIND, double>(d, x, d.lo[1] + j * d.dx[1], z, f)), d, Fl);
+            face_solve64<1>(hL, hR, geo_cast<double>(face_geo<1, KIND, double>(d, x, d.lo[1] + (j + 1) * d.dx[1], z, f + nx)),
                             d, Fh);
             if (ROLE == SWEEP_CT && own) {
                 put_transverse<1>(K.A.F[1], d.nf[1], f, Fl);
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                 __builtin_amdgcn_sched_barrier(0);
             }
             const long long f = max(i, 0) + (long long)(nx + 1) * (j + (long long)ny * k);
-            const GeoT<double> g = geo_cast<double>(face_geo<0, KIND>(
+            const GeoT<double> g = geo_cast<double>(face_geo<0, KIND, double>(
                 d, d.lo[0] + i * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1], d.lo[2] + (k + 0.5) * d.dx[2], f));
             if (ay || az)
                 face_solve64<0>(qL, qR, g, d, F);
@@ -374,7 +374,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                 sQ[v * 64 + lane] = q2[v];
             }
             const GeoT<double> g = geo_cast<double>(
-                face_geo<2, KIND>(d, d.lo[0] + (i + 0.5) * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1],
+                face_geo<2, KIND, double>(d, d.lo[0] + (i + 0.5) * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1],
                                   d.lo[2] + (k + 1) * d.dx[2], ic + (long long)nx * (j + (long long)ny * (k + 1))));
             face_solve64<2>(qL, qR, g, d, F);
             if (ROLE == SWEEP_CT && own) {
@@ -448,7 +448,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             }
             int flags = 0, iters = 0;
             if (own) {
-                flags = recover_cell(d, g, u, q, p, iters);
+                flags = recover_cell<double>(d, g, u, q, p, iters);
                 const SweepKernelArgs K2 = sweep_args();
                 const SweepArgs& B = K2.A;
                 const Dev& e = K2.d;
@@ -626,10 +626,10 @@ __global__ __launch_bounds__(256) void k_ct_update(SweepArgs A, Dev d)
                 const double us = A.Us ? A.Us[v * d.N + c] : un;
                 u[v] = us + A.a * (un - us) + A.b * (A.dt * R[v]);
             }
-            const Geo g = cell_geo<KIND>(d, d.lo[0] + (ix[0] + 0.5) * d.dx[0], d.lo[1] + (ix[1] + 0.5) * d.dx[1],
+            const Geo g = cell_geo<KIND, double>(d, d.lo[0] + (ix[0] + 0.5) * d.dx[0], d.lo[1] + (ix[1] + 0.5) * d.dx[1],
                                          d.lo[2] + (ix[2] + 0.5) * d.dx[2], c);
             int iters = 0;
-            const int flags = recover_cell(d, g, u, q, p, iters);
+            const int flags = recover_cell<double>(d, g, u, q, p, iters);
 #pragma unroll
             for (int v = 0; v < 9; ++v)
                 A.Uo[v * d.N + c] = u[v];
@@ -704,7 +704,7 @@ __global__ __launch_bounds__(256) void k_line(SweepArgs A, Dev d, LineStages rk,
     if (direct)
         __syncthreads();
     int nfail = 0, natm = 0, npf = 0, nfb = 0, itmax = 0;
-    const Geo g = geo_at<FLAT>(d, 0.0, 0.0, 0.0);
+    const Geo g = geo_at<FLAT, double>(d, 0.0, 0.0, 0.0);
 #pragma nounroll
     for (int s = 0; s < NS; ++s) {
         const double a = rk.a[s], b = rk.b[s];
@@ -728,7 +728,7 @@ __global__ __launch_bounds__(256) void k_line(SweepArgs A, Dev d, LineStages rk,
         // lanes whose stencil is still whole (the others' values are not used)
         if (lane >= 2 * (s + 1) && lane < 64 - 2 * (s + 1) && (d.bc[0] == 0 || (c >= 0 && c < n))) {
             int iters = 0;
-            const int flags = recover_cell(d, g, u, q, p, iters);
+            const int flags = recover_cell<double>(d, g, u, q, p, iters);
 #pragma unroll
             for (int v = 0; v < 9; ++v) {
                 q[v] = p[v];
