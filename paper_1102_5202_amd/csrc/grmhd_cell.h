@@ -6,6 +6,44 @@
 
 namespace grmhd {
 
+// The value of the lane to the left / right (wave-wide shift; the first / last
+// lane gets an unspecified one).
+__device__ __forceinline__ double from_left(double x)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x138, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x138, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+
+__device__ __forceinline__ double from_right(double x)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x130, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x130, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+
+// Memory accesses with a uniform 64-bit base, a 32-bit byte offset per lane and a
+// uniform one: the address arithmetic stays in the scalar unit.  NT: streaming.
+typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const double* base)
+{
+    return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0xffffffffu, 0x00027000);
+}
+
+template <bool NT = false>
+__device__ __forceinline__ double buf_load(const double* base, unsigned lane, unsigned uniform = 0)
+{
+    return __builtin_bit_cast(double,
+                              __builtin_amdgcn_raw_buffer_load_b64(buffer_at(base), lane, uniform, NT ? 2 : 0));
+}
+
+template <bool NT = false>
+__device__ __forceinline__ void buf_store(double* base, unsigned lane, double x)
+{
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2v, x), buffer_at(base), lane, 0, NT ? 2 : 0);
+}
+
 // The kernel's arguments (one struct S), loaded anew: a plane's work uses more
 // uniform values than there are scalar registers, and values kept from the
 // kernel's start would live in vector registers' lanes, one vector instruction a

@@ -1133,10 +1133,11 @@ __global__ __launch_bounds__(NT) void k_batch_evolve(BatchProb* __restrict__ pro
 }
 
 // k_batch_split: a problem's cells divided among several workgroups (parts)
-// that run at the same time, the rows in HBM.  A part walks its segment in
-// chunks of NT - 1 cells, one cell per thread (consecutive cells on
-// consecutive threads, so that row accesses are coalesced), the chunk's face
-// fluxes exchanged through LDS.  The two cells beside a segment's ends come
+// that run at the same time, the rows in HBM.  A part walks its segment with
+// consecutive cells on consecutive threads, so that row accesses are coalesced:
+// FP64 60 cells a wave, states and fluxes exchanged by lane shifts; mixed
+// precision in chunks of NT - 1 cells, one per thread, the chunk's face fluxes
+// exchanged through LDS.  The two cells beside a segment's ends come
 // from the neighbouring parts through the rows.  Parts
 // may sit on different XCDs, whose L2 caches are not kept coherent for this
 // memory, so the values that cross parts (each segment's two end cells at
@@ -1149,6 +1150,7 @@ __global__ __launch_bounds__(NT) void k_batch_evolve(BatchProb* __restrict__ pro
 // no longer reads the row they are about to overwrite).  Waits are bounded:
 // past the limit the part counts a stall (CNT_STALL) and stops instead of
 // hanging, so that a launch whose parts are not all resident ends.
+static constexpr int SPLIT_CELLS = 60;      // cells a wave updates at a time (FP64)
 static constexpr int SPLIT_SPIN = 1 << 22;   // polls of the flags before a part gives up
 
 template <typename T>
@@ -1225,27 +1227,42 @@ __device__ __forceinline__ S uniform_load(const S* p)
 
 // Workgroup w runs the parts runs[w].x .. runs[w].x + runs[w].y - 1 one
 // after another: a segment of a split problem (a run of one), or several
-// small problems packed whole (no neighbours, so no waits).  The register
-// budget of 3 waves per SIMD with a double cache, 4 with a float cache (some
-// spills either way: measured faster than fewer, larger-register waves)
-// keeps more parts resident.
+// small problems packed whole (no neighbours, so no waits).  4 waves per SIMD: a
+// float cache spills 20 registers for it, measured faster than fewer waves; FP64
+// takes 126 without spills.  Bound by vector issue and the substep's waits: the
+// 256-problem ensemble to t = 0.04 took 32.5 ms in FP64 with the chunked faces in
+// LDS (two slopes a face, 3 waves per SIMD), 28.0 ms with lane shifts, 26.5 ms at
+// 4 waves, 24.4 ms with the rows' addresses kept scalar.
 template <typename T>
-constexpr int split_waves()
-{
-    return sizeof(T) == sizeof(double) ? 3 : 4;
-}
+struct SplitArgs {
+    BatchProb* probs;
+    const BatchPart* parts;
+    const int2* runs;
+    int* flags;
+    double* U;
+    T *Us, *Prow, *Pnext;
+    Dev d;
+    int ns, max_steps;
+    unsigned long long *cnt, *span;
+};
 
 template <typename T, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(split_waves<T>(), split_waves<T>())))
-void k_batch_split(
-    BatchProb* __restrict__ probs, const BatchPart* __restrict__ parts, const int2* __restrict__ runs, int* flags,
-    double* __restrict__ U, T* __restrict__ Us, T* Prow, T* Pnext, Dev d, int ns, int max_steps,
-    unsigned long long* __restrict__ cnt, unsigned long long* __restrict__ span)
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void k_batch_split(SplitArgs<T>)
 {
+    using Args = SplitArgs<T>;
+    const Args K0 = kernel_args<Args>();
+    BatchProb* probs = K0.probs;
+    const BatchPart* parts = K0.parts;
+    const int2* runs = K0.runs;
+    int* flags = K0.flags;
+    const Dev& d = K0.d;
+    const int ns = K0.ns, max_steps = K0.max_steps;
+    unsigned long long* span = K0.span;
     const unsigned long long t_start = wall_clock64();
     __shared__ int s_ok;
     // face fluxes of a chunk of cells, double buffered: sF[b][v][f]
-    __shared__ T sF[2][9 * NT];
+    __shared__ T sF[2][sizeof(T) == sizeof(double) ? 1 : 9 * NT];
     const int2 run = runs[blockIdx.x];
     int nfail = 0, natm = 0, npf = 0, nfb = 0, itmax = 0;
     bool stalled = false;
@@ -1262,10 +1279,11 @@ void k_batch_split(
         auto edge = [&](int x) { return x < pt.c0 + 2 || x >= pt.c1 - 2; };
         auto rd = [&](const T* r, int x) { return edge(x) ? sys_load(r + x + 2) : r[x + 2]; };
         const int t = threadIdx.x;
-        double* Ub = U + 9 * pr.off;
-        T* Usb = Us + 9 * pr.off;
-        T* cur = Prow + pr.poff;
-        T* nxt = Pnext + pr.poff;
+        double* Ub = K0.U + 9 * pr.off;
+        T* Usb = K0.Us + 9 * pr.off;
+        T* const Prow = K0.Prow;
+        T* cur = K0.Prow + pr.poff;
+        T* nxt = K0.Pnext + pr.poff;
         const Geo geo = geo_at<FLAT, T>(d, 0.0, 0.0, 0.0);
         for (int i = 0; i < nsub && !stalled; ++i) {
             if (i > 0 && !split_wait(flags, pt.left, pt.right, base + i, &s_ok)) {
@@ -1275,65 +1293,137 @@ void k_batch_split(
             const int s = i % ns;
             const double a = ns == 3 ? (s == 0 ? 0.0 : (s == 1 ? 0.75 : 1.0 / 3.0)) : (s == 0 ? 0.0 : 0.5);
             const double bb = ns == 3 ? (s == 0 ? 1.0 : (s == 1 ? 0.25 : 2.0 / 3.0)) : (s == 0 ? 1.0 : 0.5);
-            // the segment in chunks of NT - 1 cells, consecutive cells on
-            // consecutive threads (coalesced rows): thread t solves the face
-            // left of cell base + t (NT faces per chunk, the last one the
-            // right face of the chunk's last cell), then updates that cell
             bool wrote_edge = false;
-            int chunk = 0;
-            for (int cb = pt.c0; cb < pt.c1; cb += NT - 1, ++chunk) {
-                const int cend = min(cb + NT - 1, pt.c1);   // cells [cb, cend), faces [cb, cend]
-                const int c = cb + t;
-                T* F = sF[chunk & 1];
-                T q[9];
-                if (c <= cend) {
-                    // face c - 1/2 from cells c-2 .. c+1 (row index + 2)
-                    T qL[9], qR[9], Fc[9];
-    #pragma unroll
-                    for (int v = 0; v < 9; ++v) {
-                        const T* r = cur + v * pitch;
-                        const T q0 = rd(r, c - 2), q1 = rd(r, c - 1), q2 = rd(r, c), q3 = rd(r, c + 1);
-                        q[v] = q2;
-                        qL[v] = q1 + mc_hslope(q0, q1, q2);
-                        qR[v] = q2 - mc_hslope(q1, q2, q3);
-                    }
-                    face_flux<0, FLAT>(qL, qR, 0.0, 0.0, 0.0, 0, d, Fc);
-    #pragma unroll
+            if constexpr (sizeof(T) == sizeof(double)) {
+                // FP64: a wave takes 60 cells at a time and exchanges reconstructed
+                // states and fluxes by lane shifts: one slope a cell instead of two a
+                // face, no LDS and no barrier within a substep
+                const int lane = t & 63;
+                for (int cb = pt.c0 + (t >> 6) * SPLIT_CELLS; cb < pt.c1; cb += NT / 64 * SPLIT_CELLS) {
+                    const int c = cb + lane - 2, cc = min(c, pt.c1 + 1);
+                    const bool own = lane >= 2 && lane < 2 + SPLIT_CELLS && c < pt.c1;
+                    const Args K = kernel_args<Args>();
+                    const Dev& d = K.d;
+                    // the rows' addresses formed anew here: kept from outside the loop they
+                    // would fill the scalar registers several times over
+                    double *Pr = cur, *Pw = nxt, *Ur = Ub, *Ui = Usb;
+                    int w = pitch;
+                    asm volatile("" : "+s"(Pr), "+s"(Pw), "+s"(Ur), "+s"(Ui), "+s"(w));
+                    double q[9], qL[9], qR[9], F[9];
+#pragma unroll
                     for (int v = 0; v < 9; ++v)
-                        F[v * NT + t] = Fc[v];
-                }
-                __syncthreads();
-                if (c < cend) {
+                        q[v] = buf_load(Pr + v * w, (unsigned)(cc + 2) * 8u);
+                    if (edge(cc)) {
+#pragma unroll
+                        for (int v = 0; v < 9; ++v)
+                            q[v] = sys_load(Pr + v * w + cc + 2);
+                    }
+#pragma unroll
+                    for (int v = 0; v < 9; ++v) {
+                        const double h = mc_hslope(from_left(q[v]), q[v], from_right(q[v]));
+                        qR[v] = q[v] - h;
+                        qL[v] = from_left(q[v] + h);
+                    }
+                    face_flux<0, FLAT>(qL, qR, 0.0, 0.0, 0.0, 0, d, F);
                     double R[9];
-    #pragma unroll
+#pragma unroll
                     for (int v = 0; v < 9; ++v)
-                        R[v] = -((double)F[v * NT + t + 1] - (double)F[v * NT + t]) * pr.idx;
-                    R[8] -= d.kappa * (double)q[8];
-                    double u[9], qg[9], p[9];
-    #pragma unroll
+                        R[v] = -(from_right(F[v]) - F[v]) * pr.idx;
+                    R[8] -= d.kappa * q[8];
+                    if (!own)
+                        continue;
+                    double u[9], p[9], un[9];
+                    const unsigned oc = (unsigned)c * 8u;
+#pragma unroll
                     for (int v = 0; v < 9; ++v) {
-                        const double un = Ub[(long long)v * n + c];
-                        const double us = s == 0 ? un : (double)Usb[(long long)v * n + c];
-                        u[v] = us + a * (un - us) + bb * (pr.dt * R[v]);
-                        qg[v] = (double)q[v];
+                        un[v] = buf_load(Ur + v * (long long)(w - 4), oc);
+                        u[v] = un[v];
                     }
+                    if (s != 0) {
+#pragma unroll
+                        for (int v = 0; v < 9; ++v)
+                            u[v] = buf_load(Ui + v * (long long)(w - 4), oc);
+                    }
+#pragma unroll
+                    for (int v = 0; v < 9; ++v)
+                        u[v] = u[v] + a * (un[v] - u[v]) + bb * (pr.dt * R[v]);
                     int iters = 0;
-                    const int fl = recover_cell<T>(d, geo, u, qg, p, iters);
+                    const int fl = recover_cell<T>(d, geo, u, q, p, iters);
                     tally(fl, iters, nfail, natm, npf, nfb, itmax);
-                    if (s == ns - 1) {
-    #pragma unroll
-                        for (int v = 0; v < 9; ++v)
-                            Ub[(long long)v * n + c] = u[v];
-                    } else {
-    #pragma unroll
-                        for (int v = 0; v < 9; ++v)
-                            Usb[(long long)v * n + c] = (T)u[v];
-                    }
+                    double* Uo = s == ns - 1 ? Ur : Ui;
+#pragma unroll
+                    for (int v = 0; v < 9; ++v)
+                        buf_store(Uo + v * (long long)(w - 4), oc, u[v]);
+                    // (a problem's end cells, which have ghost images, are edge cells)
                     if (edge(c)) {
-                        row_store_sys(nxt, pitch, n, d.bc[0], c, p);
+                        row_store_sys(Pw, w, n, d.bc[0], c, p);
                         wrote_edge = true;
                     } else {
-                        row_store(nxt, pitch, n, d.bc[0], c, p);
+#pragma unroll
+                        for (int v = 0; v < 9; ++v)
+                            buf_store(Pw + v * w, oc + 16u, p[v]);
+                    }
+                }
+            } else {
+                // the segment in chunks of NT - 1 cells, consecutive cells on
+                // consecutive threads (coalesced rows): thread t solves the face
+                // left of cell base + t (NT faces per chunk, the last one the
+                // right face of the chunk's last cell), then updates that cell
+                int chunk = 0;
+                for (int cb = pt.c0; cb < pt.c1; cb += NT - 1, ++chunk) {
+                    const int cend = min(cb + NT - 1, pt.c1);   // cells [cb, cend), faces [cb, cend]
+                    const int c = cb + t;
+                    T* F = sF[chunk & 1];
+                    T q[9];
+                    if (c <= cend) {
+                        // face c - 1/2 from cells c-2 .. c+1 (row index + 2)
+                        T qL[9], qR[9], Fc[9];
+        #pragma unroll
+                        for (int v = 0; v < 9; ++v) {
+                            const T* r = cur + v * pitch;
+                            const T q0 = rd(r, c - 2), q1 = rd(r, c - 1), q2 = rd(r, c), q3 = rd(r, c + 1);
+                            q[v] = q2;
+                            qL[v] = q1 + mc_hslope(q0, q1, q2);
+                            qR[v] = q2 - mc_hslope(q1, q2, q3);
+                        }
+                        face_flux<0, FLAT>(qL, qR, 0.0, 0.0, 0.0, 0, d, Fc);
+        #pragma unroll
+                        for (int v = 0; v < 9; ++v)
+                            F[v * NT + t] = Fc[v];
+                    }
+                    __syncthreads();
+                    if (c < cend) {
+                        double R[9];
+        #pragma unroll
+                        for (int v = 0; v < 9; ++v)
+                            R[v] = -((double)F[v * NT + t + 1] - (double)F[v * NT + t]) * pr.idx;
+                        R[8] -= d.kappa * (double)q[8];
+                        double u[9], qg[9], p[9];
+        #pragma unroll
+                        for (int v = 0; v < 9; ++v) {
+                            const double un = Ub[(long long)v * n + c];
+                            const double us = s == 0 ? un : (double)Usb[(long long)v * n + c];
+                            u[v] = us + a * (un - us) + bb * (pr.dt * R[v]);
+                            qg[v] = (double)q[v];
+                        }
+                        int iters = 0;
+                        const int fl = recover_cell<T>(d, geo, u, qg, p, iters);
+                        tally(fl, iters, nfail, natm, npf, nfb, itmax);
+                        if (s == ns - 1) {
+        #pragma unroll
+                            for (int v = 0; v < 9; ++v)
+                                Ub[(long long)v * n + c] = u[v];
+                        } else {
+        #pragma unroll
+                            for (int v = 0; v < 9; ++v)
+                                Usb[(long long)v * n + c] = (T)u[v];
+                        }
+                        if (edge(c)) {
+                            row_store_sys(nxt, pitch, n, d.bc[0], c, p);
+                            wrote_edge = true;
+                        } else {
+                            row_store(nxt, pitch, n, d.bc[0], c, p);
+                        }
                     }
                 }
             }
@@ -1372,8 +1462,8 @@ void k_batch_split(
         }
     }
     if (stalled && threadIdx.x == 0)
-        atomicAdd(&cnt[(size_t)(blockIdx.x % CNT_SLOTS) * CNT_WORDS + CNT_STALL], 1ull);
-    count_sums(cnt, nfail, natm, npf, nfb, itmax);
+        atomicAdd(&K0.cnt[(size_t)(blockIdx.x % CNT_SLOTS) * CNT_WORDS + CNT_STALL], 1ull);
+    count_sums(K0.cnt, nfail, natm, npf, nfb, itmax);
     span_record(span, t_start);
 }
 
@@ -1785,8 +1875,8 @@ hipError_t launch_batch_split(BatchProb* probs, const BatchPart* parts, int npar
 {
     hipLaunchKernelGGL(k_split_flags, dim3(blocks_for(nparts)), dim3(BLOCK), 0, s, probs, parts, nparts, flags,
                        rk_order);
-    hipLaunchKernelGGL((k_batch_split<T, BATCH_SPLIT_THREADS>), dim3(nruns), dim3(BATCH_SPLIT_THREADS), 0, s, probs,
-                       parts, runs, flags, U, Us, Prow, Pnext, d, rk_order, max_steps, cnt, span);
+    const SplitArgs<T> A{probs, parts, runs, flags, U, Us, Prow, Pnext, d, rk_order, max_steps, cnt, span};
+    hipLaunchKernelGGL((k_batch_split<T, BATCH_SPLIT_THREADS>), dim3(nruns), dim3(BATCH_SPLIT_THREADS), 0, s, A);
     return hipGetLastError();
 }
 
