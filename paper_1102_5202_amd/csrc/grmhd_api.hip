@@ -487,7 +487,10 @@ int sweep_stage(grmhd_ctx* c, const double* Pc, double* Pn, const double* Un, co
     A.dt = dt;
     A.a = a;
     A.b = b;
-    return timed(c, GRMHD_K_UPDATE, [&] { return grmhd::launch_sweep(c->kind, A, c->d, c->stream); });
+    return timed(c, GRMHD_K_UPDATE, [&] {
+        return grmhd::substep_tiled(c->d) ? grmhd::launch_substep_tiled(c->kind, A, c->d, c->stream)
+                                          : grmhd::launch_sweep(c->kind, A, c->d, c->stream);
+    });
 }
 
 // Whether a step stays in registers, stages and all: 1D grids along x, flat

@@ -68,6 +68,10 @@ struct SweepArgs {
     double dt, a, b;
     int ngrp, nseg, seg;   // set by launch_sweep
 };
+int sweep_segment(long long ngrp, int nz);
+long long sweep_groups(const Dev& d);
+bool substep_tiled(const Dev& d);
+hipError_t launch_substep_tiled(int kind, const SweepArgs& A, const Dev& d, hipStream_t s);
 hipError_t launch_sweep(int kind, const SweepArgs& A, const Dev& d, hipStream_t s);
 // One whole FP64 Runge-Kutta step of ns stages (coefficients a, b) on a 1D grid
 // along x (flat metric, MC): U and the cache P0 are advanced in place; U1, P1

@@ -35,6 +35,7 @@ static constexpr unsigned MIN_BLOCKS = 1024;   // 4 workgroups per CU: enough to
 // the fused substep kernel: tile of TX x TY columns, SUB_SEG planes per workgroup
 static constexpr int SUB_TX = 32, SUB_TY = 8, SUB_SEG = 8;
 static constexpr long long SUB_MIN_BLOCKS = 1024;
+static constexpr int SUB_RESIDENT = 512;   // two workgroups per CU
 
 // ---------------------------------------------------------------------------
 template <typename T>
@@ -556,19 +557,56 @@ __device__ __forceinline__ void tile_face(const T* sP, int dir, int base, int st
         sF[vo[v] * nslot + slot] = Fo[v];
 }
 
+// The arguments of the FP64 substep kernel, in the order of its parameters.
+struct SubstepArgs64 {
+    const double* Pc;
+    double* Pn;
+    const double* Un;
+    const double* Us;
+    double* Uout;
+    Dev d;
+    double dt, a, b;
+    unsigned long long* cnt;
+    unsigned char* fout;
+    int ntx, ntiles;
+};
+
 template <int KIND, int TX, int TY, int SEG, bool NT, typename T, typename TS, typename TO>
 __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_substep(
     const T* __restrict__ Pc, T* __restrict__ Pn, const double* Un, const TS* Us, TO* Uout, Dev d, double dt,
     double a, double b, unsigned long long* __restrict__ cnt, unsigned char* __restrict__ fout, int ntx, int ntiles)
 {
     using G = Tile<TX, TY>;
-    // The staged planes and the face fluxes are double buffered (70.8 KB of
-    // LDS, two workgroups per CU): the faces of plane k + 1 and the update of
-    // plane k share one barrier interval.
-    static_assert(sizeof(T) == sizeof(float), "mixed precision");
-    __shared__ T sP[2][9 * G::PLANE];
-    __shared__ T sFx[2][9 * G::NFX];
-    __shared__ T sFy[2][9 * G::NFY];
+    // With a float cache the staged planes and the face fluxes are double
+    // buffered (70.8 KB of LDS, still two workgroups per CU): the faces of
+    // plane k + 1 and the update of plane k then share one barrier interval.
+    // With a double cache that would take 141.7 KB, one workgroup per CU, so
+    // each plane has its staging, faces and update between two barriers, and the
+    // arguments are read again where they are used (held throughout, they spill
+    // to lanes of vector registers: 64^3, five steps, 417 -> 383 us).
+    constexpr bool DB = sizeof(T) < sizeof(double);
+    constexpr int NB = DB ? 2 : 1;
+    // mixed precision takes its parameters where they are (a copy of them changed
+    // the schedule: 128^3, five steps, 1991 us against 1977)
+    struct Held {
+        const T* __restrict__ const& Pc;
+        T* __restrict__ const& Pn;
+        const double* const& Un;
+        const TS* const& Us;
+        TO* const& Uout;
+        const Dev& d;
+        const double &dt, &a, &b;
+        unsigned char* __restrict__ const& fout;
+    };
+    auto args = [&] {
+        if constexpr (DB)
+            return Held{Pc, Pn, Un, Us, Uout, d, dt, a, b, fout};
+        else
+            return kernel_args<SubstepArgs64>();
+    };
+    __shared__ T sP[NB][9 * G::PLANE];
+    __shared__ T sFx[NB][9 * G::NFX];
+    __shared__ T sFy[NB][9 * G::NFY];
 
     const int t = threadIdx.x;
     const int tx = t % TX, ty = t / TX;
@@ -651,13 +689,14 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2)))
     }
 
     // Staging of plane k into buffer pb: the own cell (own: its value from the
-    // window) and the halo cell (hv: loaded ahead).
+    // window) and the halo cell (hv: loaded ahead with a float cache).
     T hv[9];
     auto halo_load = [&](int k) {
         if (hslot >= 0) {
+            const auto K = args();
 #pragma unroll
             for (int v = 0; v < 9; ++v)
-                hv[v] = Pc[v * d.sv + hoff + (long long)k * st];
+                hv[v] = K.Pc[v * K.d.sv + hoff + (long long)k * st];
         }
     };
     auto stage = [&](int k, int pb, const T* own, bool hv_loaded) {
@@ -667,10 +706,11 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2)))
             for (int v = 0; v < 9; ++v)
                 P[v * G::PLANE + oslot] = own[v];
         } else if (own_ghost) {
+            const auto K = args();
             const long long o = col + (long long)k * st;
 #pragma unroll
             for (int v = 0; v < 9; ++v)
-                P[v * G::PLANE + oslot] = Pc[v * d.sv + o];
+                P[v * G::PLANE + oslot] = K.Pc[v * K.d.sv + o];
         }
         if (hslot >= 0) {
             if (!hv_loaded)
@@ -687,6 +727,8 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2)))
     // row and column.  One face solver serves both axes (a loop, not
     // unrolled, keeps one copy of its code).
     auto faces = [&](int k, int pb, int fb) {
+        const auto K = args();
+        const Dev& d = K.d;
         const double zc = d.lo[2] + (k + 0.5) * d.dx[2];
         const int ntask = t >= G::NT - 64 ? 3 : 2;
 #pragma nounroll
@@ -715,22 +757,27 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
     // The update of plane k (x and y fluxes in face buffer fb): the z face
     // above the cell from the window (which moves up one plane), the flux
-    // differences, sources, RK combination and recovery.  The stage inputs
-    // are loaded first, so that the z face covers their latency, and the halo
-    // cell of plane kh is loaded before the recovery.
+    // differences, sources, RK combination and recovery.  With a float
+    // cache the stage inputs are loaded first, so that the z face covers
+    // their latency, and the halo cell of plane kh is loaded before the
+    // recovery; a double cache has no registers to spare for either.
     auto update = [&](int k, int fb, int kh) {
+        constexpr bool early = sizeof(T) < sizeof(double);
         if (!act) {
-            if (kh >= 0)
+            if (early && kh >= 0)
                 halo_load(kh);
             return;
         }
+        const auto K = args();
+        const Dev& d = K.d;
         const long long c = i + (long long)nx * (j + (long long)ny * k);
         double un[9], us[9];
-        stage_load<NT>(d, Un, Us, c, un, us);
+        if constexpr (early)
+            stage_load<NT>(d, K.Un, K.Us, c, un, us);
         T qd[9];
 #pragma unroll
         for (int v = 0; v < 9; ++v)
-            qd[v] = Pc[v * d.sv + col + (long long)(k + 2) * st];
+            qd[v] = K.Pc[v * d.sv + col + (long long)(k + 2) * st];
         T q[9], qL[9], qR[9], Fc[9];
 #pragma unroll
         for (int v = 0; v < 9; ++v) {
@@ -745,6 +792,8 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2)))
         const double zc = d.lo[2] + (k + 0.5) * d.dx[2];
         face_flux<2, KIND>(qL, qR, x, y, zc + 0.5 * d.dx[2], i + (long long)nx * (j + (long long)ny * (k + 1)), d,
                            Fc);
+        if constexpr (!early)
+            stage_load<NT>(d, K.Un, K.Us, c, un, us);
         double R[9];
 #pragma unroll
         for (int v = 0; v < 9; ++v) {
@@ -764,32 +813,43 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(2, 2)))
         }
         Geo g;
         add_sources<KIND>(d, x, y, zc, c, q, g, R);
-        if (kh >= 0)
+        if (early && kh >= 0)
             halo_load(kh);
         int iters = 0;
-        int flags = stage_finish<NT>(d, g, R, q, un, us, Uout, c, Pn, col + (long long)k * st, i, j, k, dt, a, b,
-                                     fout, iters);
+        const auto L = args();
+        int flags = stage_finish<NT>(L.d, g, R, q, un, us, L.Uout, c, L.Pn, col + (long long)k * st, i, j, k, L.dt,
+                                     L.a, L.b, L.fout, iters);
         tally(flags, iters, nfail, natm, npf, nfb, itmax);
     };
 
-    // prologue: planes k0 and k0 + 1 staged, the faces of k0 solved
-    stage(k0, 0, qb, false);
-    __syncthreads();
-    faces(k0, 0, 0);
-    if (k0 + 1 < k1)
-        stage(k0 + 1, 1, qc, false);
-    __syncthreads();
-    // plane k: the faces of k + 1, the update of k, the staging of k + 2
-    // (into the buffer plane k used; its own cell is the window's qc once
-    // the update has moved the window up)
-    for (int k = k0; k < k1; ++k) {
-        const int cur = (k - k0) & 1, nxt = cur ^ 1;
-        if (k + 1 < k1)
-            faces(k + 1, nxt, nxt);
-        update(k, cur, k + 2 < k1 ? k + 2 : -1);   // also loads the halo cell of k + 2
-        if (k + 2 < k1)
-            stage(k + 2, cur, qc, true);
+    if constexpr (DB) {
+        // prologue: planes k0 and k0 + 1 staged, the faces of k0 solved
+        stage(k0, 0, qb, false);
         __syncthreads();
+        faces(k0, 0, 0);
+        if (k0 + 1 < k1)
+            stage(k0 + 1, 1, qc, false);
+        __syncthreads();
+        // plane k: the faces of k + 1, the update of k, the staging of k + 2
+        // (into the buffer plane k used; its own cell is the window's qc once
+        // the update has moved the window up)
+        for (int k = k0; k < k1; ++k) {
+            const int cur = (k - k0) & 1, nxt = cur ^ 1;
+            if (k + 1 < k1)
+                faces(k + 1, nxt, nxt);
+            update(k, cur, k + 2 < k1 ? k + 2 : -1);   // also loads the halo cell of k + 2
+            if (k + 2 < k1)
+                stage(k + 2, cur, qc, true);
+            __syncthreads();
+        }
+    } else {
+        for (int k = k0; k < k1; ++k) {
+            stage(k, 0, qb, false);
+            __syncthreads();
+            faces(k, 0, 0);
+            __syncthreads();
+            update(k, 0, -1);
+        }
     }
     count_sums(cnt, nfail, natm, npf, nfb, itmax);
 }
@@ -1711,6 +1771,35 @@ static void launch_substep_nt(int kind, const T* Pc, T* Pn, const double* Un, co
     else
         hipLaunchKernelGGL((k_substep<STORED, TX, TY, SEG, NT, T, TS, TO>), grid, block, 0, s, Pc, Pn, Un, Us, Uout,
                            d, dt, a, b, cnt, fout, ntx, ntiles);
+}
+
+// FP64: whether the tile kernel above beats the wave-autonomous sweep on a 3D MC
+// grid with cleaning.  A tile's faces are shared in LDS (3 a cell against the
+// sweep's 4), but its workgroups take whole tiles and rounds of 512, each about
+// 44 us with two planes a workgroup, against 6e-3 (waves + 1280) (planes + 1/2) us
+// of the sweep (waves and planes as it picks them): the tile wins where it fills one
+// round.  Three steps with tile and sweep: 64^3 (512 workgroups) 238 and 276 us,
+// 60 x 64 x 64 390 and 390, 64 x 64 x 32 (256) 177 and 188, 96 x 64 x 64 (768) 356
+// and 367, 128 x 48 x 48 (576) 329 and 281, 64 x 64 x 80 (640) 553 and 510, 32^3 (64)
+// 161 and 102; 192^3 2.89 and 2.91 ms a step.
+bool substep_tiled(const Dev& d)
+{
+    if (d.nt || !d.act[2] || d.ppm || d.ct)
+        return false;
+    const long long tiles = (long long)((d.n[0] + SUB_TX - 1) / SUB_TX) * ((d.n[1] + SUB_TY - 1) / SUB_TY);
+    const long long wgs = tiles * ((d.n[2] + 1) / 2);
+    const int seg = sweep_segment(sweep_groups(d), d.n[2]);
+    const double waves = (double)(sweep_groups(d) * ((d.n[2] + seg - 1) / seg));
+    const double rounds = (double)((wgs + SUB_RESIDENT - 1) / SUB_RESIDENT);
+    return 44.0 * rounds < 0.9 * 6e-3 * (waves + 1280.0) * (seg + 0.5);
+}
+
+hipError_t launch_substep_tiled(int kind, const SweepArgs& A, const Dev& d, hipStream_t s)
+{
+    const double* Us = A.Us ? A.Us : A.Un;
+    launch_substep_nt<false, 2, double, double, double>(kind, A.Pc, A.Pn, A.Un, Us, A.Uo, d, A.dt, A.a, A.b, A.cnt,
+                                                        A.fout, s);
+    return hipGetLastError();
 }
 
 template <typename T, typename TS, typename TO>

@@ -460,7 +460,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 // waves) 43.2, 46.8, 44.5 us a substep with 1, 2, 3 planes, 96 x 80 x 72 87, 86,
 // 84, 98, 86, 93 us with 1 to 6, 192^3 0.917, 0.920, 0.933, 0.952 ms with 8, 12,
 // 16, 32.
-static int sweep_segment(long long ngrp, int nz)
+int sweep_segment(long long ngrp, int nz)
 {
     int best = 1;
     double cost = 0.0;
@@ -474,6 +474,13 @@ static int sweep_segment(long long ngrp, int nz)
     return best;
 }
 
+// Waves of a plane.
+long long sweep_groups(const Dev& d)
+{
+    const long long wx = d.act[0] ? d.n[0] + 2 : d.n[0];
+    return (wx * d.n[1] + SWEEP_USED - 1) / SWEEP_USED;
+}
+
 template <int ROLE, bool DENSE>
 static hipError_t launch_sweep_r(int kind, const SweepArgs& A, const Dev& d, hipStream_t s)
 {
@@ -484,7 +491,7 @@ static hipError_t launch_sweep_r(int kind, const SweepArgs& A, const Dev& d, hip
     if ((long long)d.px * d.py * 8 >= (1LL << 32) || total >= (1LL << 31) - 64)
         return hipErrorInvalidValue;
     SweepKernelArgs K{A, d};
-    const long long ngrp = (total + SWEEP_USED - 1) / SWEEP_USED;
+    const long long ngrp = sweep_groups(d);
     K.A.ngrp = (int)ngrp;
     K.A.seg = d.act[2] ? sweep_segment(ngrp, d.n[2]) : 1;
     K.A.nseg = (d.n[2] + K.A.seg - 1) / K.A.seg;

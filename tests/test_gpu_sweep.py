@@ -94,3 +94,25 @@ def test_line_step(G, orc, n, bc, rk):
     pb = orc.Problem(**w.problem_kwargs())
     Ur, _, _ = orc.step(pb, orc.prim2con(pb, w.P), w.P, w.dt, 3)
     assert np.all(orc.parity_error(Ua.cpu().numpy(), Ur) <= 1e-10)
+
+
+@pytest.mark.parametrize("n,bc,metric", [((64, 64, 64), WL.PERIODIC, False), ((31, 63, 127), WL.OUTFLOW, True),
+                                         ((499, 8, 63), WL.OUTFLOW, False), ((30, 15, 511), WL.PERIODIC, True)])
+def test_tiled_step(G, orc, n, bc, metric):
+    """Grids that fill one round of the tile kernel, whole and with ragged tiles and
+    segments: bitwise as recorded, and the oracle's within its bar."""
+    w = _workload(n, bc, metric, sum(n))
+    w.rk_order = 2
+    P = torch.from_numpy(w.P).to(DEV)
+    a, b = G.solver_for(w, device=DEV), G.solver_for(w, device=DEV, adjoint=True, tape_steps=1)
+    Ua, Ub = a.cons(P), b.cons(P)
+    for _ in range(2):
+        a.step(Ua, w.dt)
+        b.step_record(Ub, w.dt, 0)
+        assert torch.equal(Ua, Ub)
+    assert a.status() == b.status()
+    pb = orc.Problem(**w.problem_kwargs())
+    Ur, _, _ = orc.step(pb, orc.prim2con(pb, w.P), w.P, w.dt, 2)
+    err = orc.parity_error(Ua.cpu().numpy(), Ur)
+    print(w.name, bc, metric, err.max(), flush=True)
+    assert np.all(err <= 1e-10)
