@@ -38,6 +38,8 @@ sys.path.insert(0, ROOT)
 METRIC = "zone-updates/s per RK substep (FP64 vs mixed) at stated L1 error; adjoint/forward cost"
 HBM_PEAK_GBS = 8000.0
 KERNEL_SOURCES = ("paper_1102_5202_amd/csrc/grmhd_kernels.hip",
+                  "paper_1102_5202_amd/csrc/grmhd_sweep.hip",
+                  "paper_1102_5202_amd/csrc/grmhd_cell.h",
                   "paper_1102_5202_amd/csrc/grmhd_device.h")
 
 
@@ -124,7 +126,8 @@ def _read_csv(path):
 
 def _short(name: str) -> str:
     """Kernel class of a demangled kernel name."""
-    for key, short in (("k_substep", "update"), ("k_flux_x", "flux_x"), ("k_flux_march<1", "flux_y"),
+    for key, short in (("k_substep", "update"), ("k_sweep", "update"), ("k_line", "update"),
+                       ("k_ct_update", "ct"), ("k_flux_x", "flux_x"), ("k_flux_march<1", "flux_y"),
                        ("k_flux_march<2", "flux_z"), ("k_update", "update"), ("k_ghosts", "bc"),
                        ("k_cons", "cons"),
                        ("k_prim", "prim"), ("k_rhs", "rhs"), ("copyBuffer", "copy_probe")):

@@ -120,9 +120,9 @@ typedef enum {
  * the MC limiter and PPM).  PPM here is Colella & Woodward's interface
  * interpolation with MC-limited slopes and their monotonicity constraints
  * (no contact steepening, no flattening); it needs 3 cells on every active
- * axis, has no adjoint and no batched form, and 3D grids with it run the
- * face kernels of all three axes followed by the cell update (the fused
- * z-face + update kernel is MC only). */
+ * axis, has no adjoint and no batched form.  FP64 substeps with it are one
+ * launch; mixed precision runs the face kernels of all active axes followed
+ * by the cell update (its one-launch kernel is 3D and MC only). */
 typedef enum {
     GRMHD_RECON_MC = 0,
     GRMHD_RECON_PPM = 1
@@ -135,9 +135,10 @@ typedef enum {
  * fluxes of both face directions), which keeps the corner-centred
  * divergence sum_i d_i Bd^i unchanged to round-off in 3D.  With flux-CT Phi
  * is carried unchanged (no flux, no damping), the normal field at a face is
- * the mean of the two reconstructed ones, 3D grids run the face kernels of
- * all axes and the cell update (the fused kernel is cleaning only), and
- * there is no adjoint and no batched form. */
+ * the mean of the two reconstructed ones, and there is no adjoint and no
+ * batched form.  FP64 substeps are two launches; mixed precision runs the
+ * face kernels of all active axes, the edge corrections and the cell
+ * update. */
 typedef enum {
     GRMHD_DIV_CLEANING = 0,
     GRMHD_DIV_FLUXCT = 1
@@ -187,7 +188,7 @@ typedef enum {
     GRMHD_K_ADJ_FACE = 9, /* adjoint: face solver, one axis                  */
     GRMHD_K_ADJ_GATHER = 10, /* adjoint: reconstruction of all axes + ghost fold */
     GRMHD_K_ADJ_CELL = 11,   /* adjoint: sources + the next recovery + RK adjoint */
-    GRMHD_K_CT = 12,      /* flux-CT: edge values and the corrected field fluxes */
+    GRMHD_K_CT = 12,      /* flux-CT: edge values and the cells' field update */
     GRMHD_K_COUNT = 13
 } grmhd_kernel;
 

@@ -6,9 +6,10 @@
 // cell the flux differences, metric sources (eq. 2), SSP Runge-Kutta
 // combination, Newton recovery of the primitives with the atmosphere/floor
 // policy and the status counters.  In FP64 that is one launch of k_sweep
-// (grmhd_sweep.hip).  Here: mixed precision on 3D grids in one launch of
-// k_substep (x and y faces from planes staged in LDS, z faces from a register
-// window); mixed precision on 1D and 2D grids, with PPM or with flux-CT
+// (grmhd_sweep.hip), but for 3D grids that fill one round of k_substep.  Here:
+// k_substep, the whole substep of a 3D grid in one launch (x and y faces from
+// planes staged in LDS, z faces from a register window), for mixed precision and
+// those FP64 grids; mixed precision on 1D and 2D grids, with PPM or with flux-CT
 // (k_ct_edges, k_ct_faces), with face kernels per active axis (k_flux_x,
 // k_flux_march, k_flux_ppm) and the cell kernel k_update.  Every kernel that
 // writes primitives also writes their ghost images, so the ghost pass k_ghosts
@@ -486,8 +487,8 @@ __global__ __launch_bounds__(BLOCK) void k_update(const T* __restrict__ Fx, cons
 }
 
 // ---------------------------------------------------------------------------
-// The whole substep of a 3D grid in one kernel (mixed precision, MC
-// reconstruction, cleaning).
+// The whole substep of a 3D grid in one kernel (MC reconstruction, cleaning;
+// mixed precision, and FP64 where substep_tiled says so).
 // A workgroup owns a TX x TY tile of z columns and a segment of SEG planes and
 // walks the planes upwards.  For plane k it
 //   (1) stages the primitives of the tile and of a 2-cell halo in x and y (the

@@ -21,7 +21,8 @@
 // or as stated: face kernels and an update on 2D grids (500 x 300, five steps: 551
 // to 342 us) and with PPM (128^3, two steps: 3.59 to 2.75 ms), a kernel that
 // staged 32 x 8 tiles in LDS between two barriers a plane on 3D grids (192^3: 9.11
-// to 8.74 ms; 101 x 87 x 75, where tiles are ragged: 1.25 to 0.93 ms; 64^3: even),
+// to 8.74 ms; 101 x 87 x 75, where tiles are ragged: 1.25 to 0.93 ms; kept where its
+// tiles fill the GPU just once, substep_tiled),
 // and nine launches of a right-hand side (24 x 20 x 16: 41 to 11.5 us).  The four
 // faces a cell (one of y twice) cost 12 % more instructions than sharing would;
 // three waves per SIMD spill 30 to 50 registers and are 25 % slower.
