@@ -250,8 +250,9 @@ int grmhd_set_metric(grmhd_ctx *ctx, const double *alpha, const double *psi4, vo
 int grmhd_prim(grmhd_ctx *ctx, const double *U, double *P);
 
 /* Right-hand side L(P) = -sum_d (F_d(i+1/2) - F_d(i-1/2))/dx_d + s(P) of one
- * substep (compact form eq. 3) for the primitives P, written to R (device).
- * Loads P into the context's primitive cache, as grmhd_cons does. */
+ * substep (compact form eq. 3) for the primitives P, written to R (device; R
+ * may be P or overlap it).  Loads P into the context's primitive cache, as
+ * grmhd_cons does. */
 int grmhd_rhs(grmhd_ctx *ctx, const double *P, double *R);
 
 /* ---- Without allocation --------------------------------------------------
@@ -267,7 +268,7 @@ int grmhd_rhs(grmhd_ctx *ctx, const double *P, double *R);
  * Arguments as for grmhd_init (opts.workspace, timing, adjoint and
  * tape_steps are ignored; metric kind STORED, whose metric buffer the caller
  * would have to provide, is rejected with GRMHD_ERR_ARG) and grmhd_rhs (P
- * read, R written, device arrays [9][nz][ny][nx]); stream is the hipStream_t
+ * read, R written, device arrays [9][nz][ny][nx] that may overlap); stream is the hipStream_t
  * (as void*) the work is enqueued on, asynchronously.  Returns
  * GRMHD_ERR_WORKSPACE when grmhd_workspace_bytes(grid, opts) exceeds
  * GRMHD_NOALLOC_SCRATCH_BYTES (64 MiB: a 3D grid of about 45^3 cells in FP64,

@@ -425,21 +425,40 @@ int prim_t(grmhd_ctx* c, const double* U, double* P)
     return GRMHD_OK;
 }
 
+// Whether the caller's arrays a and b ([9][N] each) have memory in common.
+bool overlap(const grmhd_ctx* c, const double* a, const double* b)
+{
+    const uintptr_t bytes = sizeof(double) * 9 * (uintptr_t)c->L.N;
+    return (uintptr_t)a < (uintptr_t)b + bytes && (uintptr_t)b < (uintptr_t)a + bytes;
+}
+
 // Right-hand side of P.  Where k_sweep serves, one launch does all of it from P
 // itself (keep: it also loads P into the context's cache); else the cache is
-// loaded and the face kernels run.
+// loaded and the face kernels run.  A sweep from P itself stores R while other
+// waves still read P, so where the two overlap the cache is loaded first and the
+// sweep reads that (with edge values R is written by a launch of its own).
 template <typename T>
 int rhs_t(grmhd_ctx* c, const double* P, double* R, bool keep = true)
 {
-    int rc = keep || !sweeps<T>() ? prepare_t<T>(c) : GRMHD_OK;
+    const bool staged = overlap(c, P, R) && !edge_values(c);
+    int rc = keep || staged || !sweeps<T>() ? prepare_t<T>(c) : GRMHD_OK;
     if (rc)
         return rc;
     if constexpr (sweeps<T>()) {
         grmhd::SweepArgs A{};
-        A.P = P;
         A.R = R;
-        A.Pn = keep ? cache<double>(c) : nullptr;
         edge_scratch(c, A);
+        if (staged) {
+            rc = timed(c, GRMHD_K_CONS, [&] {
+                return grmhd::launch_cons(c->kind, P, (double*)nullptr, cache<T>(c), c->d, c->stream);
+            });
+            if (rc)
+                return rc;
+            A.Pc = cache<double>(c);
+        } else {
+            A.P = P;
+            A.Pn = keep ? cache<double>(c) : nullptr;
+        }
         rc = timed(c, GRMHD_K_RHS, [&] { return grmhd::launch_sweep(c->kind, A, c->d, c->stream); });
         if (rc)
             return rc;

@@ -53,9 +53,9 @@ hipError_t launch_substep(int kind, const T* Pc, T* Pn, const double* Un, const 
 // One FP64 substep, or one right-hand side (R set), of a grid: one launch, two
 // for flux-CT with edge values (grmhd_sweep.hip).
 struct SweepArgs {
-    const double* Pc;   // substep: the primitives (ghosted cache)
-    const double* P;    // right-hand side: the caller's primitives (dense)
-    double* Pn;         // the new primitives (another cache); right-hand side: P's copy, or null
+    const double* Pc;   // the primitives (ghosted cache); or, for a right-hand side that
+    const double* P;    // does not overlap them, the caller's primitives (dense)
+    double* Pn;         // the new primitives (another cache); with P set: P's copy, or null
     const double* Un;   // U^n
     const double* Us;   // U^s, or null: the first stage's, U^n
     double* Uo;         // U^(s+1)

@@ -67,8 +67,9 @@ __device__ __forceinline__ int map_cell(int c, int n, int bc)
     return c < 0 ? c + n : c - n;
 }
 
-// Where the primitives come from: the ghosted cache, or, for a right-hand side,
-// the caller's dense array with indices mapped by the boundary rule.
+// Where the primitives come from: the ghosted cache, or, for a right-hand side
+// that does not overlap them, the caller's dense array with indices mapped by the
+// boundary rule.
 template <bool DENSE, int G>
 struct Source {
     static constexpr int X = G - 1;          // cells read beside one along x
@@ -774,12 +775,14 @@ hipError_t launch_line(int ns, const double* a, const double* b, double* P0, dou
 
 hipError_t launch_sweep(int kind, const SweepArgs& A, const Dev& d, hipStream_t s)
 {
+    if (!A.R5 && A.R)
+        return A.P ? launch_sweep_r<SWEEP_RHS, true>(kind, A, d, s) : launch_sweep_r<SWEEP_RHS, false>(kind, A, d, s);
     if (!A.R5)
-        return A.R ? launch_sweep_r<SWEEP_RHS, true>(kind, A, d, s) : launch_sweep_r<SWEEP_STEP, false>(kind, A, d, s);
+        return launch_sweep_r<SWEEP_STEP, false>(kind, A, d, s);
     SweepArgs B = A;
     B.R = A.R5;
     const hipError_t e =
-        A.R ? launch_sweep_r<SWEEP_CT, true>(kind, B, d, s) : launch_sweep_r<SWEEP_CT, false>(kind, B, d, s);
+        A.P ? launch_sweep_r<SWEEP_CT, true>(kind, B, d, s) : launch_sweep_r<SWEEP_CT, false>(kind, B, d, s);
     return e == hipSuccess ? launch_ct_update(kind, A, d, s) : e;
 }
 
