@@ -384,41 +384,44 @@ struct FaceState {
     double lm, lp;       // signal speeds
 };
 
+// The fused multiply-adds are written out: left to the compiler the two states of
+// a face get different ones, and a mirrored flow other last bits.
 template <int D>
 __device__ __forceinline__ FaceState face_state(const double* q, double Bn, const GeoT<double>& g, const Dev& d)
 {
+#pragma clang fp contract(off)
     FaceState k;
     const double u0 = q[2], u1 = q[3], u2 = q[4], uD = q[2 + D];
     const double B0 = g.alpha * (D == 0 ? Bn : q[5]), B1 = g.alpha * (D == 1 ? Bn : q[6]),
                  B2 = g.alpha * (D == 2 ? Bn : q[7]);
-    const double W2 = 1.0 + g.psi4 * (u0 * u0 + u1 * u1 + u2 * u2);
+    const double W2 = fma(g.psi4, fma(u0, u0, fma(u1, u1, u2 * u2)), 1.0);
     const double iW = fast_rsqrt(W2), W = W2 * iW;
-    const double bt = g.psi4 * (B0 * u0 + B1 * u1 + B2 * u2);
-    const double b[3] = {(B0 + bt * u0) * iW, (B1 + bt * u1) * iW, (B2 + bt * u2) * iW};
-    const double b2 = (g.psi4 * (B0 * B0 + B1 * B1 + B2 * B2) + bt * bt) * iW * iW;
-    const double gp = d.gamma * q[1], w = q[0] + d.gfac * q[1];
-    const double wtot = w + b2, ptot = q[1] + 0.5 * b2;
+    const double bt = g.psi4 * fma(B0, u0, fma(B1, u1, B2 * u2));
+    const double b[3] = {fma(bt, u0, B0) * iW, fma(bt, u1, B1) * iW, fma(bt, u2, B2) * iW};
+    const double b2 = fma(g.psi4, fma(B0, B0, fma(B1, B1, B2 * B2)), bt * bt) * iW * iW;
+    const double w = fma(d.gfac, q[1], q[0]);
+    const double wtot = w + b2, ptot = fma(0.5, b2, q[1]);
     // the dispersion relation with the isotropic fast speed
     // c^2 = (gamma p + b^2) / wtot, scaled by wtot (W^2 (1 - c^2) + c^2)
-    const double an = w - gp, cn = b2 + gp;
-    const double idn = fast_rcp(W2 * an + cn);
+    const double an = fma(-d.gamma, q[1], w), cn = fma(d.gamma, q[1], b2);
+    const double idn = fast_rcp(fma(W2, an, cn));
     const double t = uD * (an * idn);
-    const double s = fast_sqrt(fmax(cn * idn * (g.ipsi4 - uD * t), 1e-290));
-    k.lp = W * t + s;
-    k.lm = W * t - s;
+    const double s = fast_sqrt(fmax(cn * idn * fma(-uD, t, g.ipsi4), 1e-290));
+    k.lp = fma(W, t, s);
+    k.lm = fma(W, t, -s);
     const double wW = wtot * W, pw = g.psi4 * wtot * uD, pb = g.psi4 * b[D], pW = g.psi4 * wW, pt = g.psi4 * bt;
     k.F[0] = q[0] * uD;
     k.U[0] = q[0] * W;
-    k.F[1] = g.alpha * (wW * uD - bt * b[D]) - k.F[0];
-    k.U[1] = g.alpha * (wW * W - ptot - bt * bt) - k.U[0];
+    k.F[1] = fma(g.alpha, fma(wW, uD, -(bt * b[D])), -k.F[0]);
+    k.U[1] = fma(g.alpha, fma(wW, W, -fma(bt, bt, ptot)), -k.U[0]);
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-        k.F[2 + j] = pw * q[2 + j] - pb * b[j];
+        k.F[2 + j] = fma(pw, q[2 + j], -(pb * b[j]));
         if (j == D)
             k.F[2 + j] += ptot;
-        k.U[2 + j] = pW * q[2 + j] - pt * b[j];
+        k.U[2 + j] = fma(pW, q[2 + j], -(pt * b[j]));
         if (j != D)
-            k.F[5 + j] = b[j] * uD - b[D] * q[2 + j];
+            k.F[5 + j] = fma(b[j], uD, -(b[D] * q[2 + j]));
     }
     k.U[5] = B0;
     k.U[6] = B1;
@@ -430,24 +433,26 @@ template <int D>
 __device__ __forceinline__ void face_solve64(const double* qL, const double* qR, const GeoT<double>& g,
                                              const Dev& d, double* Fo)
 {
+#pragma clang fp contract(off)
     // cleaning pair, or with flux-CT the mean of the normal fields (below)
     const double BnL = g.sqrtmg * qL[5 + D], BnR = g.sqrtmg * qR[5 + D];
-    const double Bs = d.ct ? 0.5 * (BnL + BnR) : 0.5 * (BnL + BnR) - 0.5 * d.ic_h * (qR[8] - qL[8]);
-    const double phs = 0.5 * (qL[8] + qR[8]) - 0.5 * d.c_h * (BnR - BnL);
+    const double Bm = 0.5 * (BnL + BnR), Bs = d.ct ? Bm : fma(-0.5 * d.ic_h, qR[8] - qL[8], Bm);
+    const double phs = fma(-0.5 * d.c_h, BnR - BnL, 0.5 * (qL[8] + qR[8]));
     const double Bn = Bs * g.isqrtmg;
     const FaceState L = face_state<D>(qL, Bn, g, d), R = face_state<D>(qR, Bn, g, d);
     const double sl = fmin(0.0, fmin(L.lm, R.lm)), sr = fmax(0.0, fmax(L.lp, R.lp));
-    // HLLE: F_L + cR (F_R - F_L) + cU (U_R - U_L); sl = 0 (sr = 0) upwinds.
-    // In this form equal fluxes and states return the flux itself, whatever
-    // the rounding of the weights, so that matter at rest in a uniform field
-    // stays exactly at rest.
-    const double cR0 = -sl * fast_rcp(sr - sl);
-    const double cR = sl == 0.0 ? 0.0 : (sr == 0.0 ? 1.0 : cR0);
-    const double cU = sl == 0.0 ? 0.0 : -sr * cR;
+    // HLLE as F + c (F' - F) + cU (U_R - U_L) from the state F of the larger weight,
+    // c <= 1/2.  Equal fluxes and states return the flux itself, whatever the
+    // rounding of the weights, so that matter at rest in a uniform field stays
+    // exactly at rest; with all signals one way (c = cU = 0) it is the upwind flux
+    // to the last bit, on either side, and a mirrored problem's the mirrored flux.
+    const bool right = -sl > sr;
+    const double ir = fast_rcp(sr - sl), lo = fmin(-sl, sr), hi = fmax(-sl, sr);
+    const double c = lo == 0.0 ? 0.0 : lo * ir, cU = -hi * c, cd = right ? -c : c;
 #pragma unroll
     for (int v = 0; v < 8; ++v)
         if (v != 5 + D)
-            Fo[v] = g.sqrtmg * (L.F[v] + cR * (R.F[v] - L.F[v]) + cU * (R.U[v] - L.U[v]));
+            Fo[v] = g.sqrtmg * fma(cU, R.U[v] - L.U[v], fma(cd, R.F[v] - L.F[v], right ? R.F[v] : L.F[v]));
     // flux-CT: no normal-field flux and no Phi flux (the transverse field
     // fluxes are replaced once the edge values are known)
     Fo[5 + D] = d.ct ? 0.0 : phs;
