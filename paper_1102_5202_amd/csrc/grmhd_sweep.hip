@@ -150,6 +150,17 @@ __device__ __forceinline__ void sweep_store(double* Pn, const Dev& d, unsigned o
     }
 }
 
+// The face solver: on 1D grids (LINE) the plain order of operations, whichever axis
+// they lie along.
+template <int D, bool LINE>
+__device__ __forceinline__ void sweep_face(double* qL, double* qR, const GeoT<double>& g, const Dev& d, double* F)
+{
+    if constexpr (LINE)
+        face_solve<D>(qL, qR, g, d, F);
+    else
+        face_solve64<D>(qL, qR, g, d, F);
+}
+
 // What a sweep leaves: the new state; the right-hand side; or, for flux-CT, the
 // flux differences and sources of mass, energy and momentum (and the flux
 // differences of the field along an inactive axis, which no edge value corrects)
@@ -166,7 +177,7 @@ __device__ __forceinline__ void put_transverse(double* F, long long nf, long lon
     F[(5 + C) * nf + f] = Fo[5 + C];
 }
 
-template <int KIND, bool PPM, int ROLE, bool DENSE>
+template <int KIND, bool PPM, int ROLE, bool DENSE, bool LINE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_sweep(SweepKernelArgs)
 {
     constexpr int G = PPM ? 3 : 2, X = G - 1;
@@ -217,7 +228,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         }
         const Geo g = face_geo<2, KIND, double>(d, d.lo[0] + (i + 0.5) * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1],
                                         d.lo[2] + k0 * d.dx[2], ic + (long long)nx * (j + (long long)ny * k0));
-        face_solve64<2>(qL, qR, geo_cast<double>(g), d, F);
+        sweep_face<2, LINE>(qL, qR, geo_cast<double>(g), d, F);
 #pragma unroll
         for (int v = 0; v < 9; ++v)
             sF[v * 64 + lane] = F[v];
@@ -257,9 +268,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             }
             const double x = d.lo[0] + (i + 0.5) * d.dx[0], z = d.lo[2] + (k + 0.5) * d.dx[2];
             const long long f = ic + (long long)nx * (j + (long long)(ny + 1) * k);
-            face_solve64<1>(lL, lR, geo_cast<double>(face_geo<1, KIND, double>(d, x, d.lo[1] + j * d.dx[1], z, f)), d, Fl);
-            face_solve64<1>(hL, hR, geo_cast<double>(face_geo<1, KIND, double>(d, x, d.lo[1] + (j + 1) * d.dx[1], z, f + nx)),
-                            d, Fh);
+            sweep_face<1, LINE>(
+                lL, lR, geo_cast<double>(face_geo<1, KIND, double>(d, x, d.lo[1] + j * d.dx[1], z, f)), d, Fl);
+            sweep_face<1, LINE>(
+                hL, hR, geo_cast<double>(face_geo<1, KIND, double>(d, x, d.lo[1] + (j + 1) * d.dx[1], z, f + nx)), d,
+                Fh);
             if (ROLE == SWEEP_CT && own) {
                 put_transverse<1>(K.A.F[1], d.nf[1], f, Fl);
                 if (j == ny - 1)
@@ -295,10 +308,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             const long long f = max(i, 0) + (long long)(nx + 1) * (j + (long long)ny * k);
             const GeoT<double> g = geo_cast<double>(face_geo<0, KIND, double>(
                 d, d.lo[0] + i * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1], d.lo[2] + (k + 0.5) * d.dx[2], f));
-            if (ay || az)
-                face_solve64<0>(qL, qR, g, d, F);
-            else
-                face_solve<0>(qL, qR, g, d, F);   // 1D grids: the plain order of operations
+            sweep_face<0, LINE>(qL, qR, g, d, F);
             if (ROLE == SWEEP_CT && used && i >= 0)
                 put_transverse<0>(K.A.F[0], d.nf[0], f, F);
 #pragma unroll
@@ -340,7 +350,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             const GeoT<double> g = geo_cast<double>(
                 face_geo<2, KIND, double>(d, d.lo[0] + (i + 0.5) * d.dx[0], d.lo[1] + (j + 0.5) * d.dx[1],
                                   d.lo[2] + (k + 1) * d.dx[2], ic + (long long)nx * (j + (long long)ny * (k + 1))));
-            face_solve64<2>(qL, qR, g, d, F);
+            sweep_face<2, LINE>(qL, qR, g, d, F);
             if (ROLE == SWEEP_CT && own) {
                 double Fp[9];
 #pragma unroll
@@ -483,8 +493,8 @@ long long sweep_groups(const Dev& d)
     return (wx * d.n[1] + SWEEP_USED - 1) / SWEEP_USED;
 }
 
-template <int ROLE, bool DENSE>
-static hipError_t launch_sweep_r(int kind, const SweepArgs& A, const Dev& d, hipStream_t s)
+template <int ROLE, bool DENSE, bool LINE>
+static hipError_t launch_sweep_l(int kind, const SweepArgs& A, const Dev& d, hipStream_t s)
 {
     const long long wx = d.act[0] ? d.n[0] + 2 : d.n[0];
     const long long total = wx * d.n[1];
@@ -501,11 +511,11 @@ static hipError_t launch_sweep_r(int kind, const SweepArgs& A, const Dev& d, hip
     if (blocks >= (1LL << 31))
         return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks), block(64);
-#define GRMHD_SWEEP(KIND)                                                                 \
-    if (d.ppm)                                                                            \
-        hipLaunchKernelGGL((k_sweep<KIND, true, ROLE, DENSE>), grid, block, 0, s, K);     \
-    else                                                                                  \
-        hipLaunchKernelGGL((k_sweep<KIND, false, ROLE, DENSE>), grid, block, 0, s, K);
+#define GRMHD_SWEEP(KIND)                                                                       \
+    if (d.ppm)                                                                                  \
+        hipLaunchKernelGGL((k_sweep<KIND, true, ROLE, DENSE, LINE>), grid, block, 0, s, K);     \
+    else                                                                                        \
+        hipLaunchKernelGGL((k_sweep<KIND, false, ROLE, DENSE, LINE>), grid, block, 0, s, K);
     if (kind == FLAT) {
         GRMHD_SWEEP(FLAT)
     } else if (kind == ISO) {
@@ -515,6 +525,16 @@ static hipError_t launch_sweep_r(int kind, const SweepArgs& A, const Dev& d, hip
     }
 #undef GRMHD_SWEEP
     return hipGetLastError();
+}
+
+template <int ROLE, bool DENSE>
+static hipError_t launch_sweep_r(int kind, const SweepArgs& A, const Dev& d, hipStream_t s)
+{
+    if constexpr (ROLE != SWEEP_CT) {   // (edge values need two active axes)
+        if (d.act[0] + d.act[1] + d.act[2] <= 1)
+            return launch_sweep_l<ROLE, DENSE, true>(kind, A, d, s);
+    }
+    return launch_sweep_l<ROLE, DENSE, false>(kind, A, d, s);
 }
 
 // The second half of a flux-CT substep or right-hand side: per cell the field's
