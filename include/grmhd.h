@@ -268,14 +268,15 @@ int grmhd_rhs(grmhd_ctx *ctx, const double *P, double *R);
  * Arguments as for grmhd_init (opts.workspace, timing, adjoint and
  * tape_steps are ignored; metric kind STORED, whose metric buffer the caller
  * would have to provide, is rejected with GRMHD_ERR_ARG) and grmhd_rhs (P
- * read, R written, device arrays [9][nz][ny][nx] that may overlap); stream is the hipStream_t
- * (as void*) the work is enqueued on, asynchronously.  Returns
- * GRMHD_ERR_WORKSPACE when grmhd_workspace_bytes(grid, opts) exceeds
- * GRMHD_NOALLOC_SCRATCH_BYTES (64 MiB: a 3D grid of about 45^3 cells in FP64,
- * 55^3 in MIXED).  Every call on one GPU uses that GPU's one scratch array
- * and clears what must start at zero itself: calls on one stream follow each
- * other safely, calls that overlap on one GPU (other streams, other host
- * threads) race. */
+ * read, R written, device arrays [9][nz][ny][nx] that may overlap); stream
+ * is the hipStream_t (as void*) the work is enqueued on, asynchronously.
+ * Returns GRMHD_ERR_WORKSPACE when the scratch of the grid and options,
+ * counted as grmhd_workspace_bytes does but with one primitive cache on 1D
+ * and 2D grids, exceeds GRMHD_NOALLOC_SCRATCH_BYTES (64 MiB: a 3D grid of
+ * about 45^3 cells in FP64, 55^3 in MIXED).  Every call on one GPU uses that
+ * GPU's one scratch array and clears what must start at zero itself: calls
+ * on one stream follow each other safely, calls that overlap on one GPU
+ * (other streams, other host threads) race. */
 #define GRMHD_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)
 int grmhd_rhs_noalloc(const grmhd_metric *metric, const grmhd_grid *grid, const grmhd_eos *eos,
                       const grmhd_opts *opts, const double *P, double *R, void *stream);

@@ -26,6 +26,7 @@ struct TimedLaunch {
 struct Layout {
     int g[3], px, py, pz;
     long long sv, N, nf[3];
+    bool sweep;   // FP64 substeps and right-hand sides by k_sweep (k_line, k_substep)
     size_t off_cnt, off_pc[3], off_us, off_f[3];
     // flux-CT: edge values of the axis pairs (x,y), (x,z), (y,z)
     bool ct = false;
@@ -66,8 +67,10 @@ bool grid_ok(const grmhd_grid* g)
     return N <= (1LL << 38);
 }
 
-// Three primitive caches, which the substeps rotate through; one is enough for
-// the scratch of grmhd_rhs_noalloc on a 1D or 2D grid, which takes no steps.
+// Primitive caches: 3D grids three, 1D and 2D ones one, and in FP64 as many as a
+// step has stages, which k_sweep's substeps rotate through (but not for the scratch of
+// grmhd_rhs_noalloc, which takes no steps).  The face kernels update one cache in
+// place and serve the grids whose planes are too large for the sweep.
 Layout make_layout(const grmhd_grid* g, size_t esize, bool adjoint = false, int ns = 3, int tape = 0,
                    int ghost = 2, bool ct = false, bool steps = true)
 {
@@ -86,12 +89,14 @@ Layout make_layout(const grmhd_grid* g, size_t esize, bool adjoint = false, int 
             nf *= g->n[e] + (e == d ? 1 : 0);
         L.nf[d] = g->n[d] > 1 ? nf : 0;
     }
+    L.sweep = esize == sizeof(double) && (adjoint || (long long)L.px * L.py < grmhd::SWEEP_PLANE);
+    const int caches = g->n[2] > 1 ? 3 : (L.sweep && steps ? ns : 1);
     size_t off = 0;
     L.off_cnt = off;
     off = round_up(off + grmhd::CNT_BYTES, 256);
     for (int b = 0; b < 3; ++b) {
         L.off_pc[b] = off;
-        if (b == 0 || g->n[2] > 1 || steps)
+        if (b < caches)
             off = round_up(off + esize * 9 * (size_t)L.sv, 256);
     }
     L.off_us = off;                  // intermediate Runge-Kutta stage state
@@ -223,9 +228,10 @@ struct grmhd_ctx {
     Layout L;
     unsigned char* ws = nullptr;
     // Primitive caches.  Pbuf[0] holds the current primitives between calls.
-    // A 3D step rotates through all three (RK3: 0 -> 1 -> 2 -> 0, RK2: 0 -> 1
-    // -> 0) so that every substep writes a cache it does not read and the step
-    // ends in Pbuf[0] (a captured step can be replayed).
+    // A step of one launch a substep rotates through them (RK3: 0 -> 1 -> 2 -> 0,
+    // RK2: 0 -> 1 -> 0) so that every substep writes a cache it does not read and
+    // the step ends in Pbuf[0] (a captured step can be replayed); the face kernels
+    // are followed by an update in place.
     void* Pbuf[3] = {nullptr, nullptr, nullptr};
     void* Us = nullptr;                     // intermediate stage state (cache type)
     void* F[3] = {nullptr, nullptr, nullptr};
@@ -319,12 +325,12 @@ bool edge_values(const grmhd_ctx* c)
     return c->d.ct && c->d.act[0] + c->d.act[1] + c->d.act[2] > 1;
 }
 
-// Which kernels a substep takes: in FP64 k_sweep; mixed precision on 3D grids
-// with MC and cleaning k_substep; else the face kernels and the update.
+// Which kernels a substep takes: in FP64 k_sweep (Layout::sweep); mixed precision on
+// 3D grids with MC and cleaning k_substep; else the face kernels and the update.
 template <typename T>
-constexpr bool sweeps()
+bool sweeps(const grmhd_ctx* c)
 {
-    return sizeof(T) == sizeof(double);
+    return sizeof(T) == sizeof(double) && c->L.sweep;
 }
 
 // The scratch of a flux-CT sweep: the face records, whose mass, energy and
@@ -374,23 +380,21 @@ int fluxes(grmhd_ctx* c, int b, int ndir)
             return rc;
         c->ghosts_ok[b] = true;
     }
-    if constexpr (!sweeps<T>()) {
-        for (int dir = 0; dir < ndir; ++dir) {
-            if (!c->d.act[dir])
-                continue;
-            rc = timed(c, GRMHD_K_FLUX_X + dir, [&] {
-                return grmhd::launch_flux(c->kind, dir, (const T*)P, faces<T>(c, dir), c->d, c->stream);
-            });
-            if (rc)
-                return rc;
-        }
-        if (edge_values(c) && ndir == 3) {
-            T* F[3] = {faces<T>(c, 0), faces<T>(c, 1), faces<T>(c, 2)};
-            T* W[3] = {(T*)c->W[0], (T*)c->W[1], (T*)c->W[2]};
-            rc = timed(c, GRMHD_K_CT, [&] { return grmhd::launch_ct(F, W, c->d, c->stream); });
-            if (rc)
-                return rc;
-        }
+    for (int dir = 0; dir < ndir; ++dir) {
+        if (!c->d.act[dir])
+            continue;
+        rc = timed(c, GRMHD_K_FLUX_X + dir, [&] {
+            return grmhd::launch_flux(c->kind, dir, (const T*)P, faces<T>(c, dir), c->d, c->stream);
+        });
+        if (rc)
+            return rc;
+    }
+    if (edge_values(c) && ndir == 3) {
+        T* F[3] = {faces<T>(c, 0), faces<T>(c, 1), faces<T>(c, 2)};
+        T* W[3] = {(T*)c->W[0], (T*)c->W[1], (T*)c->W[2]};
+        rc = timed(c, GRMHD_K_CT, [&] { return grmhd::launch_ct(F, W, c->d, c->stream); });
+        if (rc)
+            return rc;
     }
     return GRMHD_OK;
 }
@@ -440,20 +444,22 @@ bool overlap(const grmhd_ctx* c, const double* a, const double* b)
 template <typename T>
 int rhs_t(grmhd_ctx* c, const double* P, double* R, bool keep = true)
 {
-    const bool staged = overlap(c, P, R) && !edge_values(c);
-    int rc = keep || staged || !sweeps<T>() ? prepare_t<T>(c) : GRMHD_OK;
+    const bool sweep = sweeps<T>(c), staged = !sweep || (overlap(c, P, R) && !edge_values(c));
+    int rc = keep || staged ? prepare_t<T>(c) : GRMHD_OK;
     if (rc)
         return rc;
-    if constexpr (sweeps<T>()) {
+    if (staged) {
+        rc = timed(c, GRMHD_K_CONS, [&] {
+            return grmhd::launch_cons(c->kind, P, (double*)nullptr, cache<T>(c), c->d, c->stream);
+        });
+        if (rc)
+            return rc;
+    }
+    if (sweep) {
         grmhd::SweepArgs A{};
         A.R = R;
         edge_scratch(c, A);
         if (staged) {
-            rc = timed(c, GRMHD_K_CONS, [&] {
-                return grmhd::launch_cons(c->kind, P, (double*)nullptr, cache<T>(c), c->d, c->stream);
-            });
-            if (rc)
-                return rc;
             A.Pc = cache<double>(c);
         } else {
             A.P = P;
@@ -462,25 +468,18 @@ int rhs_t(grmhd_ctx* c, const double* P, double* R, bool keep = true)
         rc = timed(c, GRMHD_K_RHS, [&] { return grmhd::launch_sweep(c->kind, A, c->d, c->stream); });
         if (rc)
             return rc;
-        c->cache_valid = true;
-        c->ghosts_ok[0] = true;
-        return GRMHD_OK;
-    } else {
-        rc = timed(c, GRMHD_K_CONS, [&] {
-            return grmhd::launch_cons(c->kind, P, (double*)nullptr, cache<T>(c), c->d, c->stream);
-        });
-        if (rc)
-            return rc;
-        c->cache_valid = true;
-        c->ghosts_ok[0] = true;
-        rc = fluxes<T>(c, 0, 3);
-        if (rc)
-            return rc;
-        return timed(c, GRMHD_K_RHS, [&] {
-            return grmhd::launch_rhs(c->kind, (const T*)faces<T>(c, 0), (const T*)faces<T>(c, 1),
-                                     (const T*)faces<T>(c, 2), (const T*)cache<T>(c), R, c->d, c->stream);
-        });
     }
+    c->cache_valid = true;
+    c->ghosts_ok[0] = true;
+    if (sweep)
+        return GRMHD_OK;
+    rc = fluxes<T>(c, 0, 3);
+    if (rc)
+        return rc;
+    return timed(c, GRMHD_K_RHS, [&] {
+        return grmhd::launch_rhs(c->kind, (const T*)faces<T>(c, 0), (const T*)faces<T>(c, 1),
+                                 (const T*)faces<T>(c, 2), (const T*)cache<T>(c), R, c->d, c->stream);
+    });
 }
 
 // SSP Runge-Kutta stages: U^(s+1) = U^s + a_s (U^n - U^s) + b_s dt R(P^s)
@@ -539,9 +538,11 @@ int update_stage(grmhd_ctx* c, int src, int dst, const double* U, const TS* Us, 
                  double b)
 {
     return timed(c, GRMHD_K_UPDATE, [&] {
-        if (fused<T>(c))
-            return grmhd::launch_substep(c->kind, (const T*)cache<T>(c, src), cache<T>(c, dst), U, Us, Uout, c->d, dt,
-                                         a, b, c->cnt, (unsigned char*)nullptr, c->stream);
+        if constexpr (sizeof(T) < sizeof(double)) {
+            if (fused<T>(c))
+                return grmhd::launch_substep(c->kind, (const T*)cache<T>(c, src), cache<T>(c, dst), U, Us, Uout, c->d,
+                                             dt, a, b, c->cnt, (unsigned char*)nullptr, c->stream);
+        }
         return grmhd::launch_update(c->kind, (const T*)faces<T>(c, 0), (const T*)faces<T>(c, 1),
                                     (const T*)faces<T>(c, 2), (const T*)cache<T>(c, src), cache<T>(c, dst), U, Us,
                                     Uout, c->d, dt, a, b, c->cnt, (unsigned char*)nullptr, c->stream);
@@ -559,12 +560,10 @@ int step_t(grmhd_ctx* c, double* U, double dt)
     // (for flux-CT with the face fluxes corrected in between).  The first stage
     // reads U^n as its stage state; the intermediate stage state has the cache
     // type (float in the mixed path); the last stage writes U.
-    const bool rotate = sweeps<T>() || fused<T>(c);
+    const bool sweep = sweeps<T>(c), rotate = sweep || fused<T>(c);
     T* Us = (T*)c->Us;
-    if constexpr (sweeps<T>()) {
-        if (in_line(c))
-            return line_step(c, U, dt, nullptr, nullptr);
-    }
+    if (sweep && in_line(c))
+        return line_step(c, U, dt, nullptr, nullptr);
     for (int s = 0; s < ns; ++s) {
         const bool first = s == 0, last = s == ns - 1;
         const int src = rotate ? s : 0;
@@ -572,16 +571,16 @@ int step_t(grmhd_ctx* c, double* U, double dt)
         int rc = fluxes<T>(c, src, rotate ? 0 : 3);
         if (rc)
             return rc;
-        if constexpr (sweeps<T>()) {
-            rc = sweep_stage(c, cache<double>(c, src), cache<double>(c, dst), U, first ? nullptr : Us, last ? U : Us, dt,
+        if (sweep) {
+            double* Ud = (double*)c->Us;
+            rc = sweep_stage(c, cache<double>(c, src), cache<double>(c, dst), U, first ? nullptr : Ud, last ? U : Ud, dt,
                              A[s], B[s], nullptr);
+        } else if (first) {
+            rc = update_stage<T>(c, src, dst, U, (const double*)U, Us, dt, A[s], B[s]);
+        } else if (!last) {
+            rc = update_stage<T>(c, src, dst, U, (const T*)Us, Us, dt, A[s], B[s]);
         } else {
-            if (first)
-                rc = update_stage<T>(c, src, dst, U, (const double*)U, Us, dt, A[s], B[s]);
-            else if (!last)
-                rc = update_stage<T>(c, src, dst, U, (const T*)Us, Us, dt, A[s], B[s]);
-            else
-                rc = update_stage<T>(c, src, dst, U, (const T*)Us, U, dt, A[s], B[s]);
+            rc = update_stage<T>(c, src, dst, U, (const T*)Us, U, dt, A[s], B[s]);
         }
         if (rc)
             return rc;

@@ -68,6 +68,14 @@ struct SweepArgs {
     double dt, a, b;
     int ngrp, nseg, seg;   // set by launch_sweep
 };
+// Cache positions of a plane from which FP64 grids take the face kernels and the
+// update in place (2D grids: 3D ones of such planes exceed the card's memory).
+// The sweep's byte offsets within a plane are 32 bits wide, which 2^29 positions
+// would fill, and its further caches (144 B a cell with RK3) would keep grids of up
+// to 8e8 cells off the card that the face kernels' one cache leaves room for
+// (16384 x 16340 swept: 84 ms an RK3 step, 116 GB of workspace; 16384 x 16384 by the
+// face kernels: 115 ms, 77 GB).
+static constexpr long long SWEEP_PLANE = 1LL << 28;
 int sweep_segment(long long ngrp, int nz);
 long long sweep_groups(const Dev& d);
 bool substep_tiled(const Dev& d);

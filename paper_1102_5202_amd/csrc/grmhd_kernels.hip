@@ -2026,6 +2026,7 @@ hipError_t launch_batch_evolve(int shape, int lds, size_t lds_bytes, BatchProb* 
                                                hipStream_t);
 GRMHD_INSTANTIATE_BATCH(double)
 GRMHD_INSTANTIATE_BATCH(float)
+GRMHD_INSTANTIATE_UPDATE(double, double, double)
 GRMHD_INSTANTIATE_UPDATE(float, double, float)
 GRMHD_INSTANTIATE_UPDATE(float, float, float)
 GRMHD_INSTANTIATE_UPDATE(float, float, double)
@@ -2036,16 +2037,15 @@ GRMHD_INSTANTIATE_SUBSTEP(float, float, double)
 #define GRMHD_INSTANTIATE(T)                                                                            \
     template hipError_t launch_fill<T>(T*, long long, double, hipStream_t);                             \
     template hipError_t launch_ghosts<T>(T*, const Dev&, hipStream_t);                                  \
+    template hipError_t launch_flux<T>(int, int, const T*, T*, const Dev&, hipStream_t);               \
+    template hipError_t launch_ct<T>(T* const*, T* const*, const Dev&, hipStream_t);                   \
+    template hipError_t launch_rhs<T>(int, const T*, const T*, const T*, const T*, double*, const Dev&,  \
+                                      hipStream_t);                                                     \
     template hipError_t launch_cons<T>(int, const double*, double*, T*, const Dev&, hipStream_t);      \
     template hipError_t launch_prim<T>(int, const double*, double*, T*, const Dev&, unsigned long long*, \
                                        hipStream_t);
 GRMHD_INSTANTIATE(double)
 GRMHD_INSTANTIATE(float)
 
-// mixed precision only
-template hipError_t launch_flux<float>(int, int, const float*, float*, const Dev&, hipStream_t);
-template hipError_t launch_ct<float>(float* const*, float* const*, const Dev&, hipStream_t);
-template hipError_t launch_rhs<float>(int, const float*, const float*, const float*, const float*, double*, const Dev&,
-                                      hipStream_t);
 
 }  // namespace grmhd

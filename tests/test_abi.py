@@ -358,3 +358,31 @@ def test_rhs_noalloc_validates_before_touching_a_device(lib):
     big = lib.make_grid((64, 64, 64), (0, 0, 0), (1, 1, 1), (0, 0, 0))
     assert L.grmhd_workspace_bytes(C.byref(big), C.byref(o)) > lib.NOALLOC_SCRATCH_BYTES
     assert L.grmhd_rhs_noalloc(C.byref(m), C.byref(big), C.byref(e), C.byref(o), fake, fake, None) == ERR_WS
+
+
+def test_workspace_holds_the_caches_its_path_uses(lib):
+    """Primitive caches of 1D and 2D grids: one for the face kernels (mixed
+    precision, and FP64 planes of 2^28 positions and more), in FP64 otherwise one
+    for each stage of a step; 3D grids three."""
+    L = lib.load()
+    up = lambda x: (x + 255) // 256 * 256
+
+    def parts(n, esize, caches):
+        g = [2 if v > 1 else 0 for v in n]
+        sv = (n[0] + 2 * g[0] + 7) // 8 * 8 * (n[1] + 2 * g[1]) * (n[2] + 2 * g[2])
+        N = n[0] * n[1] * n[2]
+        faces = [N // v * (v + 1) if v > 1 else 0 for v in n]
+        return (up(8 * 16 * 256) + caches * up(esize * 9 * sv) + up(esize * 9 * N)
+                + sum(up(esize * 9 * f) for f in faces))
+
+    for n in ((300, 1, 1), (1, 40, 1), (50, 40, 1), (1, 7, 9), (16, 8, 6), (1 << 14, (1 << 14) - 16, 1),
+              (1 << 14, 1 << 14, 1)):
+        grid = lib.make_grid(n, (0, 0, 0), (1, 1, 1), (0, 1, 1))
+        for rk in (2, 3):
+            o = lib.Opts()
+            o.rk_order = rk
+            big = n[0] * n[1] >= 1 << 28
+            fp64 = 3 if n[2] > 1 else (1 if big else rk)
+            assert L.grmhd_workspace_bytes(C.byref(grid), C.byref(o)) == parts(n, 8, fp64), (n, rk)
+            o.precision = 1
+            assert L.grmhd_workspace_bytes(C.byref(grid), C.byref(o)) == parts(n, 4, 3 if n[2] > 1 else 1), (n, rk)
