@@ -1038,6 +1038,28 @@ int grmhd_rhs_noalloc(const grmhd_metric* metric, const grmhd_grid* grid, const 
     return c.mixed ? rhs_t<float>(&c, P, R, false) : rhs_t<double>(&c, P, R, false);
 }
 
+// Which kernel an FP64 step of this grid and these options takes, for the library's
+// own tests (no part of the C ABI): 0 the face kernels and the update, 1 the sweep,
+// 2 the tile kernel, 3 the line (flat metric); -1 for invalid arguments.
+int grmhd_internal_step_kernel(const grmhd_grid* grid, const grmhd_opts* opts)
+{
+    if (!grid_ok(grid) || !opts || !opts_fit(grid, opts) || opts->precision != GRMHD_FP64)
+        return -1;
+    grmhd_ctx c;
+    c.L = make_layout(grid, sizeof(double), false, 3, 0, ghost_width(opts), opts->divergence == GRMHD_DIV_FLUXCT);
+    c.d = Dev{};
+    c.kind = grmhd::FLAT;
+    for (int a = 0; a < 3; ++a) {
+        c.d.n[a] = grid->n[a];
+        c.d.act[a] = grid->n[a] > 1;
+    }
+    c.d.ppm = opts->reconstruction == GRMHD_RECON_PPM;
+    c.d.ct = opts->divergence == GRMHD_DIV_FLUXCT;
+    if (!sweeps<double>(&c))
+        return 0;
+    return in_line(&c) ? 3 : (grmhd::substep_tiled(c.d) ? 2 : 1);
+}
+
 int grmhd_step(grmhd_ctx* c, double* U, double dt)
 {
     if (!c || !U || !std::isfinite(dt))

@@ -76,7 +76,7 @@ struct SweepArgs {
 // (16384 x 16340 swept: 84 ms an RK3 step, 116 GB of workspace; 16384 x 16384 by the
 // face kernels: 115 ms, 77 GB).
 static constexpr long long SWEEP_PLANE = 1LL << 28;
-int sweep_segment(long long ngrp, int nz);
+static constexpr int SWEEP_RESIDENT = 2048;   // waves: two per SIMD
 long long sweep_groups(const Dev& d);
 bool substep_tiled(const Dev& d);
 hipError_t launch_substep_tiled(int kind, const SweepArgs& A, const Dev& d, hipStream_t s);

@@ -1775,24 +1775,26 @@ static void launch_substep_nt(int kind, const T* Pc, T* Pn, const double* Un, co
 }
 
 // FP64: whether the tile kernel above beats the wave-autonomous sweep on a 3D MC
-// grid with cleaning.  A tile's faces are shared in LDS (3 a cell against the
-// sweep's 4), but its workgroups take whole tiles and rounds of 512, each about
-// 44 us with two planes a workgroup, against 6e-3 (waves + 1280) (planes + 1/2) us
-// of the sweep (waves and planes as it picks them): the tile wins where it fills one
-// round.  Three steps with tile and sweep: 64^3 (512 workgroups) 238 and 276 us,
-// 60 x 64 x 64 390 and 390, 64 x 64 x 32 (256) 177 and 188, 96 x 64 x 64 (768) 356
-// and 367, 128 x 48 x 48 (576) 329 and 281, 64 x 64 x 80 (640) 553 and 510, 32^3 (64)
-// 161 and 102; 192^3 2.89 and 2.91 ms a step.
+// grid with cleaning.  Its faces are shared in LDS (3 a cell against the sweep's 4),
+// but its workgroups take whole tiles of 32 x 8 x 2 cells and whole rounds of the
+// resident 512; the sweep's waves (62 positions of one plane each on these sizes)
+// come in rounds of 2048.  The line: the tiles fit one round and the sweep would need
+// a third one.  Microseconds a substep with tile and sweep, flat (curved 8 % more on
+// both; stored metric, 64^3: 47.1 and 52.7), over 410 grids of 12 to 192 cells an
+// axis, whole and ragged tiles:
+//   taken      64^3 39.1 and 46.4, 63^3 35.5 and 41.0, 128 x 64 x 32 36.2 and 41.8,
+//              96 x 94 x 28 36.5 and 42.1, 31 x 128 x 63 37.0 and 41.3, 96 x 16 x 164
+//              40.4 and 40.1; the ratio of the 29 measured grids 0.84 to 1.01, mean 0.90
+//   left       62^3 (3968 waves) 35.4 and 36.8, 64 x 64 x 48 33.3 and 34.5, 32^3 23.6
+//              and 13.7, 65 x 64 x 64 (768 workgroups) 50.4 and 41.2, 96^3 115 and 112,
+//              64 x 64 x 128 (two full rounds) 64.5 and 73.7, but 64 x 56 x 142 74.6 and
+//              69.3 and 128 x 103 x 38 73.3 and 69.7; mean of the ratio 1.28
 bool substep_tiled(const Dev& d)
 {
-    if (d.nt || !d.act[2] || d.ppm || d.ct)
+    if (!d.act[2] || d.ppm || d.ct)
         return false;
     const long long tiles = (long long)((d.n[0] + SUB_TX - 1) / SUB_TX) * ((d.n[1] + SUB_TY - 1) / SUB_TY);
-    const long long wgs = tiles * ((d.n[2] + 1) / 2);
-    const int seg = sweep_segment(sweep_groups(d), d.n[2]);
-    const double waves = (double)(sweep_groups(d) * ((d.n[2] + seg - 1) / seg));
-    const double rounds = (double)((wgs + SUB_RESIDENT - 1) / SUB_RESIDENT);
-    return 44.0 * rounds < 0.9 * 6e-3 * (waves + 1280.0) * (seg + 0.5);
+    return tiles * ((d.n[2] + 1) / 2) <= SUB_RESIDENT && sweep_groups(d) * d.n[2] > 2 * SWEEP_RESIDENT;
 }
 
 hipError_t launch_substep_tiled(int kind, const SweepArgs& A, const Dev& d, hipStream_t s)

@@ -472,7 +472,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 // waves) 43.2, 46.8, 44.5 us a substep with 1, 2, 3 planes, 96 x 80 x 72 87, 86,
 // 84, 98, 86, 93 us with 1 to 6, 192^3 0.917, 0.920, 0.933, 0.952 ms with 8, 12,
 // 16, 32.
-int sweep_segment(long long ngrp, int nz)
+static int sweep_segment(long long ngrp, int nz)
 {
     int best = 1;
     double cost = 0.0;

@@ -386,3 +386,33 @@ def test_workspace_holds_the_caches_its_path_uses(lib):
             assert L.grmhd_workspace_bytes(C.byref(grid), C.byref(o)) == parts(n, 8, fp64), (n, rk)
             o.precision = 1
             assert L.grmhd_workspace_bytes(C.byref(grid), C.byref(o)) == parts(n, 4, 3 if n[2] > 1 else 1), (n, rk)
+
+
+def test_which_kernel_an_fp64_step_takes(lib):
+    """The tile kernel where its workgroups (32 x 8 columns, two planes) fit one
+    round of 512 and the sweep's waves (62 positions of a plane, a ghost at either
+    end of a row) need a third round of 2048; the line for 1D grids along x; the face
+    kernels for planes of 2^28 positions; the sweep for the rest."""
+    L = lib.load()
+    FACES, SWEEP, TILE, LINE = range(4)
+
+    def route(n, recon=0, div=0):
+        o = lib.Opts()
+        o.rk_order, o.reconstruction, o.divergence = 3, recon, div
+        g = lib.make_grid(n, (0, 0, 0), (1, 1, 1), (0, 0, 0))
+        return L.grmhd_internal_step_kernel(C.byref(g), C.byref(o))
+
+    for n in ((64, 64, 64), (63, 63, 63), (31, 128, 63), (96, 94, 28), (32, 56, 143), (128, 112, 18), (160, 136, 12)):
+        assert route(n) == TILE, n
+        assert route(n, recon=1) == SWEEP and route(n, div=1) == SWEEP
+    for n in ((62, 62, 62), (65, 64, 64), (64, 64, 66), (64, 64, 48), (32, 32, 32), (499, 8, 63), (96, 96, 96),
+              (192, 192, 192), (500, 300, 1), (1, 400, 1), (1, 1, 400), (1, 512, 512), (16384, 16000, 1)):
+        assert route(n) == SWEEP, n
+    assert route((400, 1, 1)) == LINE and route((400, 1, 1), recon=1) == SWEEP
+    assert route((16384, 16384, 1)) == FACES
+    rng = np.random.default_rng(4)
+    for _ in range(2000):
+        n = tuple(int(v) for v in np.exp(rng.uniform(np.log(8), np.log(200), 3)).round())
+        tiles = -(-n[0] // 32) * -(-n[1] // 8) * -(-n[2] // 2)
+        waves = -(-(n[0] + 2) * n[1] // 62) * n[2]
+        assert route(n) == (TILE if tiles <= 512 and waves > 4096 else SWEEP), n

@@ -116,3 +116,30 @@ def test_tiled_step(G, orc, n, bc, metric):
     err = orc.parity_error(Ua.cpu().numpy(), Ur)
     print(w.name, bc, metric, err.max(), flush=True)
     assert np.all(err <= 1e-10)
+
+
+@pytest.mark.parametrize("n,bc,metric", [((63, 63, 63), WL.OUTFLOW, True), ((31, 128, 63), WL.PERIODIC, True),
+                                         ((96, 94, 28), WL.OUTFLOW, False), ((32, 56, 143), WL.PERIODIC, False)])
+def test_ragged_tiles(G, orc, n, bc, metric):
+    """Grids the tile kernel takes (the choice itself is asserted) whose last tiles
+    are cut short along x or y and whose last segment has one plane: against the
+    oracle, and bitwise as recorded."""
+    import ctypes as C
+    o = G.Opts()
+    o.rk_order = 2
+    assert G.load().grmhd_internal_step_kernel(C.byref(G.make_grid(n, (0,) * 3, (1,) * 3, (bc,) * 3)), C.byref(o)) == 2
+    w = _workload(n, bc, metric, sum(n))
+    w.rk_order = 2
+    P = torch.from_numpy(w.P).to(DEV)
+    a, b = G.solver_for(w, device=DEV), G.solver_for(w, device=DEV, adjoint=True, tape_steps=1)
+    Ua, Ub = a.cons(P), b.cons(P)
+    for _ in range(2):
+        a.step(Ua, w.dt)
+        b.step_record(Ub, w.dt, 0)
+        assert torch.equal(Ua, Ub)
+    assert a.status() == b.status()
+    pb = orc.Problem(**w.problem_kwargs())
+    Ur, _, _ = orc.step(pb, orc.prim2con(pb, w.P), w.P, w.dt, 2)
+    err = orc.parity_error(Ua.cpu().numpy(), Ur)
+    print(w.name, bc, metric, err.max(), flush=True)
+    assert np.all(err <= 1e-10)
