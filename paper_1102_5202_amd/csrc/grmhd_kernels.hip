@@ -24,6 +24,9 @@
 //
 // Threads are mapped over faces (cells), x fastest, so every load and store of
 // the structure-of-arrays buffers is coalesced.
+#include <cstddef>
+#include <type_traits>
+
 #include "grmhd_cell.h"
 #include "grmhd_device.h"
 #include "grmhd_internal.h"
@@ -558,7 +561,8 @@ __device__ __forceinline__ void tile_face(const T* sP, int dir, int base, int st
         sF[vo[v] * nslot + slot] = Fo[v];
 }
 
-// The arguments of the FP64 substep kernel, in the order of its parameters.
+// The arguments of the FP64 substep kernel, in the order of its parameters
+// (checked where it is launched).
 struct SubstepArgs64 {
     const double* Pc;
     double* Pn;
@@ -1797,8 +1801,46 @@ bool substep_tiled(const Dev& d)
     return tiles * ((d.n[2] + 1) / 2) <= SUB_RESIDENT && sweep_groups(d) * d.n[2] > 2 * SWEEP_RESIDENT;
 }
 
+// k_substep's FP64 instances read their arguments again through SubstepArgs64: its
+// fields are the kernel's parameters, each where the launch puts it.
+template <class... A>
+struct ArgOffsets {
+    size_t at[sizeof...(A)];
+    constexpr ArgOffsets() : at{}
+    {
+        const size_t size[] = {sizeof(A)...}, align[] = {alignof(A)...};
+        size_t off = 0;
+        for (size_t i = 0; i < sizeof...(A); ++i) {
+            off = (off + align[i] - 1) / align[i] * align[i];
+            at[i] = off;
+            off += size[i];
+        }
+    }
+};
+
+template <class... A>
+constexpr bool args_as_read(void (*)(A...))
+{
+    using S = SubstepArgs64;
+    if (!std::is_same<void(A...), void(decltype(S::Pc), decltype(S::Pn), decltype(S::Un), decltype(S::Us),
+                                       decltype(S::Uout), Dev, double, double, double, decltype(S::cnt),
+                                       decltype(S::fout), int, int)>::value)
+        return false;
+    const ArgOffsets<A...> o;
+    const size_t f[] = {offsetof(S, Pc), offsetof(S, Pn), offsetof(S, Un), offsetof(S, Us),   offsetof(S, Uout),
+                        offsetof(S, d),  offsetof(S, dt), offsetof(S, a),  offsetof(S, b),    offsetof(S, cnt),
+                        offsetof(S, fout), offsetof(S, ntx), offsetof(S, ntiles)};
+    if (sizeof f / sizeof f[0] != sizeof...(A))
+        return false;
+    for (size_t i = 0; i < sizeof...(A); ++i)
+        if (f[i] != o.at[i])
+            return false;
+    return true;
+}
+
 hipError_t launch_substep_tiled(int kind, const SweepArgs& A, const Dev& d, hipStream_t s)
 {
+    static_assert(args_as_read(&k_substep<FLAT, SUB_TX, SUB_TY, 2, false, double, double, double>), "argument layout");
     const double* Us = A.Us ? A.Us : A.Un;
     launch_substep_nt<false, 2, double, double, double>(kind, A.Pc, A.Pn, A.Un, Us, A.Uo, d, A.dt, A.a, A.b, A.cnt,
                                                         A.fout, s);
