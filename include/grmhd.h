@@ -427,10 +427,13 @@ int grmhd_free(grmhd_ctx *ctx);
 
 /* For callers that check the library's compiled device arithmetic: on the
  * device arrays x, y (n doubles each), out[0..n) = x / y, out[n..2n) =
- * sqrt(x), out[2n..3n) = 1 / sqrt(x), evaluated as the kernels evaluate these
+ * sqrt(x), out[2n..3n) = 1 / sqrt(x), evaluated as the build flags make these
  * operations (FP64 division as a Newton-refined reciprocal times the
- * numerator; see the build flags), to be compared with correctly rounded
- * results.  out (3n doubles) is written, asynchronously on stream. */
+ * numerator), to be compared with correctly rounded results.  (The FP64
+ * path's metric, 2D and 3D faces, ensemble and Newton iteration take shorter
+ * forms of the reciprocal and the square roots, within 1 and 2 ulp, which the
+ * library's tests check apart.)  out (3n doubles) is written, asynchronously
+ * on stream. */
 int grmhd_device_arith(const double *x, const double *y, double *out, long long n, void *stream);
 
 /* Static description of an error code. */

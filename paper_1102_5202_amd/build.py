@@ -14,7 +14,9 @@ is a reciprocal refined by two Newton steps times the numerator instead of
 the correctly rounded division sequence (``-freciprocal-math
 -fapprox-func`` on the device side: within 2 ulp, about 4 fewer
 instructions per division; 1.5 % on a step, measured); double square roots
-are unchanged.
+written as such keep the library's form.  (The FP64 path's metric, face solver
+and Newton iteration call shorter forms of their own, ``fast_rcp``,
+``fast_rsqrt`` and ``fast_sqrt`` in ``grmhd_device.h``.)
 """
 from __future__ import annotations
 

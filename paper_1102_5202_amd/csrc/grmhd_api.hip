@@ -1223,6 +1223,15 @@ int grmhd_device_arith(const double* x, const double* y, double* out, long long 
     return grmhd::launch_arith(x, y, out, n, (hipStream_t)stream) == hipSuccess ? GRMHD_OK : GRMHD_ERR_HIP;
 }
 
+// The FP64 path's reciprocal and square roots on x (n doubles) into out (3 n), for the
+// library's own tests (no part of the C ABI).
+int grmhd_internal_roots(const double* x, double* out, long long n, void* stream)
+{
+    if (!x || !out || n < 0 || n > (1LL << 30))
+        return GRMHD_ERR_ARG;
+    return grmhd::launch_roots(x, out, n, (hipStream_t)stream) == hipSuccess ? GRMHD_OK : GRMHD_ERR_HIP;
+}
+
 const char* grmhd_strerror(int code)
 {
     switch (code) {

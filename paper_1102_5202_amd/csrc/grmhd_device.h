@@ -42,9 +42,14 @@ struct Dev {
     const double* mf[3];
 };
 
-// Square roots and the reciprocal of positive normal doubles, without the range
-// scaling of the library forms (arguments here are far from the ends of the
-// exponent range): the hardware estimate refined to within an ulp.
+// Reciprocal square root, square root (x > 0) and reciprocal (either sign: the
+// recovery's determinant is negative) of normal doubles, the hardware estimate of
+// 2^-23 refined once: a third-order Householder step (Taylor series of (1 - e)^-1/2
+// and (1 - e)^-1 in the estimate's residual e), for the square root a Goldschmidt step
+// and a residual correction.  Within 1 ulp (the reciprocal square root 2) for
+// 1e-290 <= |x| <= 1e290 (checked).  Unlike the library's square roots they
+// scale nothing and give NaN for 0 and infinity (as this build's division does): no
+// argument here is either, but for states that are not finite anyway.
 __device__ __forceinline__ double fast_rsqrt(double x)
 {
     const double y = __builtin_amdgcn_rsq(x);

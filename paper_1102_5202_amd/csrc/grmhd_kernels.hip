@@ -1554,6 +1554,24 @@ static inline unsigned blocks_for(long long n)
     return (unsigned)((n + BLOCK - 1) / BLOCK);
 }
 
+// The shorter forms of the FP64 path: out = [1 / x, 1 / sqrt|x|, sqrt|x|].
+__global__ __launch_bounds__(BLOCK) void k_roots(const double* __restrict__ x, double* __restrict__ out, long long n)
+{
+    const long long t = (long long)blockIdx.x * BLOCK + threadIdx.x;
+    if (t >= n)
+        return;
+    out[t] = fast_rcp(x[t]);
+    out[n + t] = fast_rsqrt(fabs(x[t]));
+    out[2 * n + t] = fast_sqrt(fabs(x[t]));
+}
+
+hipError_t launch_roots(const double* x, double* out, long long n, hipStream_t s)
+{
+    if (n > 0)
+        hipLaunchKernelGGL(k_roots, dim3(blocks_for(n)), dim3(BLOCK), 0, s, x, out, n);
+    return hipGetLastError();
+}
+
 hipError_t launch_arith(const double* x, const double* y, double* out, long long n, hipStream_t s)
 {
     if (n > 0)
