@@ -436,6 +436,14 @@ bool overlap(const grmhd_ctx* c, const double* a, const double* b)
     return (uintptr_t)a < (uintptr_t)b + bytes && (uintptr_t)b < (uintptr_t)a + bytes;
 }
 
+// The second launch of a flux-CT sweep.
+int edge_update(grmhd_ctx* c, const grmhd::SweepArgs& A)
+{
+    if (!A.R5)
+        return GRMHD_OK;
+    return timed(c, GRMHD_K_CT, [&] { return grmhd::launch_ct_update(c->kind, A, c->d, c->stream); });
+}
+
 // Right-hand side of P.  Where k_sweep serves, one launch does all of it from P
 // itself (keep: it also loads P into the context's cache); else the cache is
 // loaded and the face kernels run.  A sweep from P itself stores R while other
@@ -466,6 +474,8 @@ int rhs_t(grmhd_ctx* c, const double* P, double* R, bool keep = true)
             A.Pn = keep ? cache<double>(c) : nullptr;
         }
         rc = timed(c, GRMHD_K_RHS, [&] { return grmhd::launch_sweep(c->kind, A, c->d, c->stream); });
+        if (rc == GRMHD_OK)
+            rc = edge_update(c, A);
         if (rc)
             return rc;
     }
@@ -505,10 +515,11 @@ int sweep_stage(grmhd_ctx* c, const double* Pc, double* Pn, const double* Un, co
     A.dt = dt;
     A.a = a;
     A.b = b;
-    return timed(c, GRMHD_K_UPDATE, [&] {
+    const int rc = timed(c, GRMHD_K_UPDATE, [&] {
         return grmhd::substep_tiled(c->d) ? grmhd::launch_substep_tiled(c->kind, A, c->d, c->stream)
                                           : grmhd::launch_sweep(c->kind, A, c->d, c->stream);
     });
+    return rc ? rc : edge_update(c, A);
 }
 
 // Whether a step stays in registers, stages and all: 1D grids along x, flat

@@ -51,8 +51,8 @@ template <typename T, typename TS, typename TO>
 hipError_t launch_substep(int kind, const T* Pc, T* Pn, const double* Un, const TS* Us, TO* Uout, const Dev& d,
                           double dt, double a, double b, unsigned long long* cnt, unsigned char* fout,
                           hipStream_t s);
-// One FP64 substep, or one right-hand side (R set), of a grid: one launch, two
-// for flux-CT with edge values (grmhd_sweep.hip).
+// One FP64 substep, or one right-hand side (R set), of a grid: launch_sweep, and with
+// edge values (flux-CT, R5 set) launch_ct_update after it (grmhd_sweep.hip).
 struct SweepArgs {
     const double* Pc;   // the primitives (ghosted cache); or, for a right-hand side that
     const double* P;    // does not overlap them, the caller's primitives (dense)
@@ -82,6 +82,7 @@ long long sweep_groups(const Dev& d);
 bool substep_tiled(const Dev& d);
 hipError_t launch_substep_tiled(int kind, const SweepArgs& A, const Dev& d, hipStream_t s);
 hipError_t launch_sweep(int kind, const SweepArgs& A, const Dev& d, hipStream_t s);
+hipError_t launch_ct_update(int kind, const SweepArgs& A, const Dev& d, hipStream_t s);
 // One whole FP64 Runge-Kutta step of ns stages (coefficients a, b) on a 1D grid
 // along x (flat metric, MC): U and the cache P0 are advanced in place; U1, P1
 // scratch of their shapes.  stages, fout (null unless recorded): the caches of the

@@ -632,7 +632,7 @@ __global__ __launch_bounds__(256) void k_ct_update(SweepArgs A, Dev d)
         count_sums(A.cnt, nfail, natm, npf, nfb, itmax);
 }
 
-static hipError_t launch_ct_update(int kind, const SweepArgs& A, const Dev& d, hipStream_t s)
+hipError_t launch_ct_update(int kind, const SweepArgs& A, const Dev& d, hipStream_t s)
 {
     const dim3 grid((unsigned)((d.N + 255) / 256)), block(256);
 #define GRMHD_CT(KIND)                                                           \
@@ -801,9 +801,7 @@ hipError_t launch_sweep(int kind, const SweepArgs& A, const Dev& d, hipStream_t 
         return launch_sweep_r<SWEEP_STEP, false>(kind, A, d, s);
     SweepArgs B = A;
     B.R = A.R5;
-    const hipError_t e =
-        A.P ? launch_sweep_r<SWEEP_CT, true>(kind, B, d, s) : launch_sweep_r<SWEEP_CT, false>(kind, B, d, s);
-    return e == hipSuccess ? launch_ct_update(kind, A, d, s) : e;
+    return A.P ? launch_sweep_r<SWEEP_CT, true>(kind, B, d, s) : launch_sweep_r<SWEEP_CT, false>(kind, B, d, s);
 }
 
 }  // namespace grmhd

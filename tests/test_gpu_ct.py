@@ -135,3 +135,19 @@ def test_mixed_periodic_flat_box(G, orc):
     err = rel_l1(U, Ur)
     say("flux-CT mixed periodic box rel-L1", err, st)
     assert np.all(err[:8] <= MIXED_BAR)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_edge_update_is_timed_as_its_own_class(G, precision):
+    """grmhd_timing counts the edge values and the field update apart from the
+    substep's other launches, in either precision."""
+    w = WL.config2(n=(20, 16, 12), nsteps=1)
+    s = G.solver_for(w, device=DEV, divergence="fluxct", precision=precision, timing=True)
+    P = torch.from_numpy(np.ascontiguousarray(w.P)).to(DEV)
+    U = s.cons(P)
+    s.timing(reset=True)
+    s.step(U, w.dt)
+    s.rhs(P)
+    t = s.timing()
+    assert t["ct"][1] == w.rk_order + 1 and t["ct"][0] > 0.0
+    assert t["update"][1] == w.rk_order and t["rhs"][1] == 1
