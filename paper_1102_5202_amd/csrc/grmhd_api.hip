@@ -70,7 +70,7 @@ bool grid_ok(const grmhd_grid* g)
 // Primitive caches: 3D grids three, 1D and 2D ones one, and in FP64 as many as a
 // step has stages, which k_sweep's substeps rotate through (but not for the scratch of
 // grmhd_rhs_noalloc, which takes no steps).  The face kernels update one cache in
-// place and serve the grids whose planes are too large for the sweep.
+// place and serve the grids whose planes are too large or too small for the sweep.
 Layout make_layout(const grmhd_grid* g, size_t esize, bool adjoint = false, int ns = 3, int tape = 0,
                    int ghost = 2, bool ct = false, bool steps = true)
 {
@@ -89,7 +89,7 @@ Layout make_layout(const grmhd_grid* g, size_t esize, bool adjoint = false, int 
             nf *= g->n[e] + (e == d ? 1 : 0);
         L.nf[d] = g->n[d] > 1 ? nf : 0;
     }
-    L.sweep = esize == sizeof(double) && (adjoint || (long long)L.px * L.py < grmhd::SWEEP_PLANE);
+    L.sweep = esize == sizeof(double) && grmhd::swept((long long)L.px * L.py, g->n[2], ghost == 3);
     const int caches = g->n[2] > 1 ? 3 : (L.sweep && steps ? ns : 1);
     size_t off = 0;
     L.off_cnt = off;
@@ -499,10 +499,27 @@ const double RK2A[2] = {0.0, 0.5};
 const double RK2B[2] = {1.0, 0.5};
 
 // One FP64 substep: the primitives Pc to Pn, the stage state Us
-// (null: U^n) to Uo.
-int sweep_stage(grmhd_ctx* c, const double* Pc, double* Pn, const double* Un, const double* Us, double* Uo, double dt,
-                double a, double b, unsigned char* fout)
+// (null: U^n) to Uo.  By the face kernels only for recorded and recomputed steps
+// (which know no flux-CT): grmhd_step updates its one cache in place.
+int stage64(grmhd_ctx* c, const double* Pc, double* Pn, const double* Un, const double* Us, double* Uo, double dt,
+            double a, double b, unsigned char* fout)
 {
+    if (!c->L.sweep) {
+        for (int dir = 0; dir < 3; ++dir) {
+            if (!c->d.act[dir])
+                continue;
+            const int rc = timed(c, GRMHD_K_FLUX_X + dir, [&] {
+                return grmhd::launch_flux(c->kind, dir, Pc, (double*)c->F[dir], c->d, c->stream);
+            });
+            if (rc)
+                return rc;
+        }
+        return timed(c, GRMHD_K_UPDATE, [&] {
+            return grmhd::launch_update(c->kind, (const double*)c->F[0], (const double*)c->F[1],
+                                        (const double*)c->F[2], Pc, Pn, Un, Us ? Us : Un, Uo, c->d, dt, a, b, c->cnt,
+                                        fout, c->stream);
+        });
+    }
     grmhd::SweepArgs A{};
     A.Pc = Pc;
     A.Pn = Pn;
@@ -584,7 +601,7 @@ int step_t(grmhd_ctx* c, double* U, double dt)
             return rc;
         if (sweep) {
             double* Ud = (double*)c->Us;
-            rc = sweep_stage(c, cache<double>(c, src), cache<double>(c, dst), U, first ? nullptr : Ud, last ? U : Ud, dt,
+            rc = stage64(c, cache<double>(c, src), cache<double>(c, dst), U, first ? nullptr : Ud, last ? U : Ud, dt,
                              A[s], B[s], nullptr);
         } else if (first) {
             rc = update_stage<T>(c, src, dst, U, (const double*)U, Us, dt, A[s], B[s]);
@@ -635,7 +652,7 @@ int adj_recompute(grmhd_ctx* c, const double* U, double dt, const double* A, con
     if (rc)
         return rc;
     for (int s = 0; s < ns; ++s) {
-        rc = sweep_stage(c, c->Ac[s], c->Ac[s + 1], U, s == 0 ? nullptr : c->Aus, c->Aus, dt, A[s], B[s],
+        rc = stage64(c, c->Ac[s], c->Ac[s + 1], U, s == 0 ? nullptr : c->Aus, c->Aus, dt, A[s], B[s],
                          c->Aflags + (size_t)s * c->L.N);
         if (rc)
             return rc;
@@ -728,7 +745,7 @@ int step_record(grmhd_ctx* c, double* U, double dt, int slot)
         return GRMHD_ERR_HIP;
     double* Us = (double*)c->Us;
     unsigned char* fl = tape_flags(c, slot);
-    if (in_line(c)) {
+    if (c->L.sweep && in_line(c)) {
         double* stages[3] = {tape_cache(c, slot, 1), tape_cache(c, slot, 2), ns == 3 ? tape_cache(c, slot, 3) : nullptr};
         rc = line_step(c, U, dt, stages, fl);
         if (rc == GRMHD_OK)
@@ -736,7 +753,7 @@ int step_record(grmhd_ctx* c, double* U, double dt, int slot)
         return rc;
     }
     for (int s = 0; s < ns; ++s) {
-        rc = sweep_stage(c, tape_cache(c, slot, s), tape_cache(c, slot, s + 1), U, s == 0 ? nullptr : Us,
+        rc = stage64(c, tape_cache(c, slot, s), tape_cache(c, slot, s + 1), U, s == 0 ? nullptr : Us,
                          s == ns - 1 ? U : Us, dt, A[s], B[s], fl + (size_t)s * c->L.N);
         if (rc)
             return rc;

@@ -77,6 +77,17 @@ struct SweepArgs {
 // (16384 x 16340 swept: 84 ms an RK3 step, 116 GB of workspace; 16384 x 16384 by the
 // face kernels: 115 ms, 77 GB).
 static constexpr long long SWEEP_PLANE = 1LL << 28;
+// Whether the sweep takes an FP64 grid of nz planes of `plane` cache positions.  Many
+// planes of a few positions each leave most of its lanes idle, where the face kernels'
+// threads run along z.  Microseconds with sweep and face kernels: RK3 step 1 x 1 x
+// 30000 (8 positions) 324 and 138, 3 x 3 (56) 595 and 457, 1 x 4 (64) 510 and 395, 1 x 8
+// (96) 592 and 652, 1 x 1 x 10000 129 and 128; with PPM 1 x 1 x 30000 444 and 55, 3 x 3
+// (144) 1098 and 703, 1 x 16 (176) 1033 and 1125, 1 x 1 x 3000 82 and 46, x 1000 44 and 45.
+inline bool swept(long long plane, int nz, bool ppm)
+{
+    const bool thin = plane <= (ppm ? 160 : 64) && nz >= (ppm ? 2048 : 16384);
+    return plane < SWEEP_PLANE && !thin;
+}
 static constexpr int SWEEP_RESIDENT = 2048;   // waves: two per SIMD
 long long sweep_groups(const Dev& d);
 bool substep_tiled(const Dev& d);

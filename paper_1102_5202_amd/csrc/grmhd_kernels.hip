@@ -108,7 +108,7 @@ __device__ __forceinline__ void face_store(T* qL, T* qR, double x, double y, dou
                                            T* __restrict__ F, long long NF, long long f)
 {
     T Fo[9];
-    face_flux<D, KIND>(qL, qR, x, y, z, f, d, Fo);
+    face_solve<D>(qL, qR, geo_cast<T>(face_geo<D, KIND, T>(d, x, y, z, f)), d, Fo);   // the plain order in FP64 too
     // the face records are read back by another kernel, not by this one: on
     // large grids (NT) nontemporal stores
     if constexpr (NT) {

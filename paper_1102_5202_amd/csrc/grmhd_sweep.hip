@@ -498,8 +498,7 @@ static hipError_t launch_sweep_l(int kind, const SweepArgs& A, const Dev& d, hip
 {
     const long long wx = d.act[0] ? d.n[0] + 2 : d.n[0];
     const long long total = wx * d.n[1];
-    // byte offsets within a plane are 32-bit (such grids take the face kernels;
-    // an adjoint context of that size exceeds the card's memory several times)
+    // byte offsets within a plane are 32-bit (such grids take the face kernels)
     if ((long long)d.px * d.py * 8 >= (1LL << 32) || total >= (1LL << 31) - 64)
         return hipErrorInvalidValue;
     SweepKernelArgs K{A, d};

@@ -410,6 +410,14 @@ def test_which_kernel_an_fp64_step_takes(lib):
         assert route(n) == SWEEP, n
     assert route((400, 1, 1)) == LINE and route((400, 1, 1), recon=1) == SWEEP
     assert route((16384, 16384, 1)) == FACES
+    # long grids along z of few positions a plane (8 to 64; with PPM 8 to 160)
+    for n in ((1, 1, 16384), (1, 4, 20000), (3, 3, 20000), (32, 1, 20000)):
+        assert route(n) == FACES and route(n, div=1) == FACES, n
+    for n in ((1, 1, 2048), (1, 8, 3000), (3, 3, 2048), (32, 1, 2100)):
+        assert route(n) == SWEEP and route(n, recon=1) == FACES, n
+    for n in ((1, 1, 16383), (1, 8, 20000), (6, 5, 30000), (1, 20000, 1)):
+        assert route(n) == SWEEP, n
+    assert route((1, 1, 2047), recon=1) == SWEEP and route((1, 16, 30000), recon=1) == SWEEP
     rng = np.random.default_rng(4)
     for _ in range(2000):
         n = tuple(int(v) for v in np.exp(rng.uniform(np.log(8), np.log(200), 3)).round())

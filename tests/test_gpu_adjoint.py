@@ -322,12 +322,13 @@ def test_autograd_evolve_tape_reused_in_between(G):
     assert torch.isfinite(P0b.grad).all()
 
 
-@pytest.mark.parametrize("k,axis", [(1, 1), (3, 2), (6, 2), (7, 1)])
-def test_step_adjoint_of_riemann_problems_along_other_axes(G, orc, AD, k, axis):
+@pytest.mark.parametrize("k,axis,n", [(1, 1, 64), (3, 2, 64), (6, 2, 64), (7, 1, 64), (1, 2, 16384)])
+def test_step_adjoint_of_riemann_problems_along_other_axes(G, orc, AD, k, axis, n):
     """Matter at rest beside a jump sits on the limiter's kinks, where the branch
     follows the rounding of the forward pass: a 1D problem along y or z takes the
-    same order of operations as one along x."""
-    w = WL.config1(k, n=64, axis=axis)
+    same order of operations as one along x (a long one along z by the face
+    kernels)."""
+    w = WL.config1(k, n=n, axis=axis)
     pb = orc.Problem(**w.problem_kwargs())
     U0, P0, _ = orc.step(pb, orc.prim2con(pb, w.P), w.P, w.dt, 1)
     rng = np.random.default_rng(3)
