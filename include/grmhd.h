@@ -136,9 +136,9 @@ typedef enum {
  * divergence sum_i d_i Bd^i unchanged to round-off in 3D.  With flux-CT Phi
  * is carried unchanged (no flux, no damping), the normal field at a face is
  * the mean of the two reconstructed ones, and there is no adjoint and no
- * batched form.  FP64 substeps are two launches; mixed precision runs the
- * face kernels of all active axes, the edge corrections and the cell
- * update. */
+ * batched form.  FP64 substeps are two launches; mixed precision (and an FP64
+ * grid too thin or too large for the sweep) runs the face kernels of all
+ * active axes, the edge corrections and the cell update. */
 typedef enum {
     GRMHD_DIV_CLEANING = 0,
     GRMHD_DIV_FLUXCT = 1
@@ -174,7 +174,10 @@ typedef struct {
     int max_newton_it;      /* most 2D Newton iterations any cell needed */
 } grmhd_stats;
 
-/* Kernel classes reported by grmhd_timing(). */
+/* Kernel classes reported by grmhd_timing().  An FP64 substep or right-hand
+ * side is one launch, faces and all, under UPDATE or RHS (flux-CT: a second one
+ * under CT), a mixed one on 3D grids with MC and cleaning too; FLUX_X to FLUX_Z
+ * count only where face kernels run. */
 typedef enum {
     GRMHD_K_BC = 0,       /* ghost-zone fill of the primitive cache          */
     GRMHD_K_FLUX_X = 1,   /* reconstruction + face physics + HLLE, x faces   */

@@ -369,11 +369,12 @@ __device__ __forceinline__ bool finite(double x)
 // one reciprocal square root, one reciprocal and one square root remain of two
 // square roots and three divisions; per face 96 vector instructions fewer, and
 // the 192^3 step went from 9.70 to 9.11 ms for three steps, the 64^3 one from
-// 446 to 417 us for five.  face_solve keeps the plain order: FP32 (its results
+// 446 to 417 us for five (the upwind flux exact on either side, two selects a
+// component, took back 1 %).  face_solve keeps the plain order: FP32 (its results
 // are the mixed path's stated ones) and 1D grids along any axis, where matter at
 // rest beside a jump sits on the limiter's kinks and the derivative there follows
-// the rounding of that order (the 1D ensemble, which has no derivative, takes the
-// regrouped form).
+// the rounding of that order, and the face kernels (the 1D ensemble, which has no
+// derivative, takes the regrouped form).
 //
 // One state of a face along D, in the variables the HLLE flux needs:
 // with Bh = alpha B, bt = alpha b^t = Bh.u and b^i = (Bh^i + bt u^i) / W every flux

@@ -44,7 +44,7 @@ template <typename T, typename TS, typename TO>
 hipError_t launch_update(int kind, const T* Fx, const T* Fy, const T* Fz, const T* Pc, T* Pn, const double* Un,
                          const TS* Us, TO* Uout, const Dev& d, double dt, double a, double b,
                          unsigned long long* cnt, unsigned char* fout, hipStream_t s);
-// The whole substep of a 3D grid (mixed precision, MC, cleaning) in one launch:
+// The whole substep of a mixed-precision 3D grid (MC, cleaning) in one launch:
 // faces of all three axes, flux differences, sources, RK combination and recovery; reads
 // the primitives from Pc, writes the new ones (with ghost images) to Pn.
 template <typename T, typename TS, typename TO>

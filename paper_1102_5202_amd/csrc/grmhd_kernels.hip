@@ -6,11 +6,12 @@
 // cell the flux differences, metric sources (eq. 2), SSP Runge-Kutta
 // combination, Newton recovery of the primitives with the atmosphere/floor
 // policy and the status counters.  In FP64 that is one launch of k_sweep
-// (grmhd_sweep.hip), but for 3D grids that fill one round of k_substep.  Here:
-// k_substep, the whole substep of a 3D grid in one launch (x and y faces from
-// planes staged in LDS, z faces from a register window), for mixed precision and
-// those FP64 grids; mixed precision on 1D and 2D grids, with PPM or with flux-CT
-// (k_ct_edges, k_ct_faces), with face kernels per active axis (k_flux_x,
+// (grmhd_sweep.hip), but for 3D grids that fill one round of k_substep
+// (substep_tiled).  Here: k_substep, the whole substep of a 3D grid in one launch
+// (x and y faces from planes staged in LDS, z faces from a register window), for
+// mixed precision and those FP64 grids; mixed precision on 1D and 2D grids, with PPM
+// or with flux-CT (k_ct_edges, k_ct_faces), and FP64 grids whose planes are too thin
+// or too large for the sweep (swept), with face kernels per active axis (k_flux_x,
 // k_flux_march, k_flux_ppm) and the cell kernel k_update.  Every kernel that
 // writes primitives also writes their ghost images, so the ghost pass k_ghosts
 // runs only for caches filled otherwise.  Also here: the stored metric's set-up
@@ -1294,7 +1295,8 @@ __device__ __forceinline__ S uniform_load(const S* p)
 // after another: a segment of a split problem (a run of one), or several
 // small problems packed whole (no neighbours, so no waits).  4 waves per SIMD: a
 // float cache spills 20 registers for it, measured faster than fewer waves; FP64
-// takes 126 without spills.  Bound by vector issue and the substep's waits: the
+// takes 124, none spilled to memory, but keeps 104 scalar values in lanes of them
+// (float 86).  Bound by vector issue and the substep's waits: the
 // 256-problem ensemble to t = 0.04 took 32.5 ms in FP64 with the chunked faces in
 // LDS (two slopes a face, 3 waves per SIMD), 28.0 ms with lane shifts, 26.5 ms at
 // 4 waves, 24.4 ms with the rows' addresses kept scalar.

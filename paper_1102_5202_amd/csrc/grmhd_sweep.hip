@@ -16,16 +16,18 @@
 // go to another cache with their ghost images.  Flux-CT leaves the cell to a
 // second launch (k_ct_update).
 //
-// Bound by vector issue (about 2600 instructions a cell and plane, 65 % busy at
-// two waves per SIMD, 213 to 229 registers).  It replaced, for three RK3 steps
-// or as stated: face kernels and an update on 2D grids (500 x 300, five steps: 551
-// to 342 us) and with PPM (128^3, two steps: 3.59 to 2.75 ms), a kernel that
-// staged 32 x 8 tiles in LDS between two barriers a plane on 3D grids (192^3: 9.11
-// to 8.74 ms; 101 x 87 x 75, where tiles are ragged: 1.25 to 0.93 ms; kept where its
-// tiles fill the GPU just once, substep_tiled),
-// and nine launches of a right-hand side (24 x 20 x 16: 41 to 11.5 us).  The four
-// faces a cell (one of y twice) cost 12 % more instructions than sharing would;
-// three waves per SIMD spill 30 to 50 registers and are 25 % slower.
+// Bound by vector issue and by memory together: a curved 192^3 substep (0.90 ms)
+// takes 2,900 vector instructions a cell (issue 58 % of the time, at two waves per
+// SIMD) and moves 487 B a cell (336 by design), at 79 % of a copy's rate; with PPM
+// (128^3) 5,000 instructions and 620 B.  185 to 222 registers for a substep, to 230
+// for flux-CT, to 256 for the 1D instances (the curved one spills 2).  It replaced,
+// for three RK3 steps or as stated: face kernels and an update on 2D grids (500 x
+// 300, five steps: 551 to 342 us) and with PPM (128^3, two steps: 3.59 to 2.75 ms), a
+// kernel that staged 32 x 8 tiles in LDS between two barriers a plane on 3D grids
+// (192^3: 9.11 to 8.8 ms; 101 x 87 x 75, where tiles are ragged: 1.25 to 0.93 ms; kept
+// where it takes a round less, substep_tiled), and nine launches of a right-hand
+// side (24 x 20 x 16: 41 to 11.5 us).  Three waves per SIMD spilled 30 to 50 registers
+// and took 13.3 ms for the 9.1 of two.
 #include "grmhd_cell.h"
 #include "grmhd_device.h"
 #include "grmhd_internal.h"
@@ -544,9 +546,10 @@ static hipError_t launch_sweep_r(int kind, const SweepArgs& A, const Dev& d, hip
 // the corrected fluxes are F^a(Bd^b) = -1/2 and F^b(Bd^a) = +1/2 the sum of the
 // edge values at a face's two edges.  Every cell forms its four edge values per
 // pair itself, the lower neighbour's term first, so that the cells around an edge
-// agree on its value to the last bit; the caches serve the repeated reads.  The
-// two launches move 560 B a cell; face records, edge values and corrected fluxes
-// as arrays of their own moved 1160 B in six launches.
+// agree on its value to the last bit; the caches serve the repeated reads.  By
+// design the two launches move 560 B a cell (measured 290 and 420 at 128^3); face
+// records, edge values and corrected fluxes as arrays of their own took 1160 B in
+// six launches (three RK2 steps of the 128^3 box 3310 us, 2465 now).
 template <int KIND, bool RHS>
 __global__ __launch_bounds__(256) void k_ct_update(SweepArgs A, Dev d)
 {
